@@ -2542,17 +2542,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 ?
                   threadIdx.x >> 6, threadIdx.x & 63);
 }
 
-// q bias folded at creation: c_q = W_q^t phi(0) + b_q with phi(0)_d = cos(beta_d).
-__global__ void k_fold_q_bias(int M, int D_t, const float *__restrict__ W_q, const float *b_q,
-                              const double *__restrict__ beta, float *c_q)   // may alias b_q
+// q bias folded: c_q = W_q^t phi(0) + b_q with phi(0)_d = cos(beta_d), one
+// wavefront per output (lanes over d, fp64 sums).  c_q may alias b_q.
+__device__ __forceinline__ void fold_q_bias(int k, int M, int D_t, const float *W_q,
+                                            const float *b_q, const double *beta, float *c_q)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= M)
-        return;
-    double acc = b_q[k];
-    for (int d = 0; d < D_t; ++d)
+    const int lane = threadIdx.x & 63;
+    double acc = 0.0;
+    for (int d = lane; d < D_t; d += kWave)
         acc += (double)W_q[(int64_t)k * (M + D_t) + M + d] * cos(beta[d]);
-    c_q[k] = (float)acc;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        acc += __shfl_xor(acc, o, kWave);
+    if (lane == 0)
+        c_q[k] = (float)(acc + (double)b_q[k]);
+}
+
+__global__ __launch_bounds__(256) void k_fold_q_bias(int M, int D_t, const float *W_q,
+                                                     const float *b_q, const double *beta,
+                                                     float *c_q)
+{
+    const int k = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+    if (k < M)
+        fold_q_bias(k, M, D_t, W_q, b_q, beta, c_q);
 }
 
 bool attn_lds_opt_in(int bytes, int fold_bytes, int agg_bytes)
@@ -2921,7 +2933,7 @@ extern "C" tgm_status_t tgm_model_create(const tgm_model_desc *d, const tgm_weig
         if ((st = upload(m->out_b, ob.data(), ob.size() * 4)) != TGM_OK) break;
         if ((st = upload(m->b_o, w->b_o, 4 * M)) != TGM_OK) break;
         if ((st = upload(wq_dev, w->W_q, sizeof(float) * (size_t)M * Dq)) != TGM_OK) break;
-        hipLaunchKernelGGL(k_fold_q_bias, dim3(cdiv(M, 64)), dim3(64), 0, s, M, D_t, wq_dev,
+        hipLaunchKernelGGL(k_fold_q_bias, dim3(cdiv(M, 4)), dim3(256), 0, s, M, D_t, wq_dev,
                            m->pbias, m->beta, m->pbias);
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
             st = TGM_EDEVICE;
@@ -3455,54 +3467,68 @@ __device__ __forceinline__ float pack_src(const PackSrc &p, int n, int k)
     return p.W[blk][(int64_t)rr * p.ldw[blk] + c];
 }
 
-// out[((kc NB + nb) 64 + lane) 4 + j] = src(16 nb + lane % 16, 16 kc + 4 (lane / 16) + j),
-// zero outside [0, n_out) x [0, K): the layout of pack_b
-__global__ __launch_bounds__(256) void k_pack(PackSrc p, int n_out, int K, int KC, int NB,
-                                              float *__restrict__ out)
-{
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= (int64_t)KC * NB * kWave * 4)
-        return;
-    const int j = (int)(t & 3), lane = (int)((t >> 2) & 63);
-    const int64_t blk = t >> 8;
-    const int nb = (int)(blk % NB), kc = (int)(blk / NB);
-    const int k = 16 * kc + 4 * (lane >> 4) + j, n = 16 * nb + (lane & 15);
-    out[t] = (k < K && n < n_out) ? pack_src(p, n, k) : 0.f;
-}
+// One packed operand: out[((kc NB + nb) 64 + lane) 4 + j] = src(16 nb + lane % 16,
+// 16 kc + 4 (lane / 16) + j), zero outside [0, n_out) x [0, K): the layout of
+// pack_b.  Its elements are the workgroups [blk0, next job's blk0), kPackPer
+// elements each.
+constexpr int kPackPer = 1024;
+struct PackJob {
+    PackSrc src;
+    int n_out, K, NB, blk0;
+    int64_t total;
+    float *out;
+};
 
-// GRU biases [4][MP]: b_ir + b_hr, b_iz + b_hz, b_in, b_hn (JODIE: 0, 0, b_ih, b_hh)
-__global__ void k_pack_gru_bias(int M, int MP, int gates, const float *__restrict__ b_ih,
-                                const float *__restrict__ b_hh, float *__restrict__ out)
+// Every operand of a repack in one launch: the packed matrices, then the
+// query bias (one wavefront per unit), then one workgroup of plain biases.
+// As a launch per operand (16 of them) the step spent about 100 us here, 24
+// of them in a query-bias kernel with one thread per unit.
+constexpr int kPackJobs = 12;
+struct RepackArgs {
+    PackJob job[kPackJobs];
+    int n_jobs, cq0, small0;   // first workgroups of the query bias and of the biases
+    int M, MP, D_t;
+    const float *b_ih, *b_hh, *W_q, *b_q, *b_k, *b_v, *b_o;
+    const double *beta;
+    float *gru_bias, *pbias, *out_bo;
+};
+
+__global__ __launch_bounds__(256) void k_repack(RepackArgs a)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= M)
+    const int blk = blockIdx.x, M = a.M;
+    if (blk >= a.small0) {   // GRU biases [4][MP]: b_ir + b_hr, b_iz + b_hz, b_in, b_hn
+        for (int k = threadIdx.x; k < M; k += blockDim.x) {
+            a.gru_bias[k] = a.b_ih[k] + a.b_hh[k];
+            a.gru_bias[a.MP + k] = a.b_ih[M + k] + a.b_hh[M + k];
+            a.gru_bias[2 * a.MP + k] = a.b_ih[2 * M + k];
+            a.gru_bias[3 * a.MP + k] = a.b_hh[2 * M + k];
+            a.pbias[M + k] = a.b_k[k];
+            a.pbias[2 * M + k] = a.b_v[k];
+            a.out_bo[k] = a.b_o[k];
+        }
         return;
-    if (gates == 3) {
-        out[k] = b_ih[k] + b_hh[k];
-        out[MP + k] = b_ih[M + k] + b_hh[M + k];
-        out[2 * MP + k] = b_ih[2 * M + k];
-        out[3 * MP + k] = b_hh[2 * M + k];
-    } else {
-        out[2 * MP + k] = b_ih[k];
-        out[3 * MP + k] = b_hh[k];
     }
-}
-
-__global__ void k_copy_f32(const float *__restrict__ src, float *__restrict__ dst, int n)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n)
-        dst[k] = src[k];
-}
-
-tgm_status_t pack_launch(const PackSrc &p, int n_out, int K, int KC, int NB, void *out,
-                         hipStream_t s)
-{
-    const int64_t n = (int64_t)KC * NB * kWave * 4;
-    if (n > 0)
-        TGM_LAUNCH(k_pack, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, p, n_out, K, KC, NB,
-                   (float *)out);
-    return TGM_OK;
+    if (blk >= a.cq0) {
+        const int k = (blk - a.cq0) * 4 + (int)(threadIdx.x >> 6);
+        if (k < M)
+            fold_q_bias(k, M, a.D_t, a.W_q, a.b_q, a.beta, a.pbias);
+        return;
+    }
+    int i = 0;
+    while (i + 1 < a.n_jobs && blk >= a.job[i + 1].blk0)
+        ++i;
+    const PackJob &p = a.job[i];
+#pragma unroll
+    for (int u = 0; u < kPackPer / 256; ++u) {
+        const int64_t t = (int64_t)(blk - p.blk0) * kPackPer + u * 256 + threadIdx.x;
+        if (t >= p.total)
+            continue;
+        const int j = (int)(t & 3), lane = (int)((t >> 2) & 63);
+        const int b = (int)(t >> 8);
+        const int nb = b % p.NB, kc = b / p.NB;
+        const int k = 16 * kc + 4 * (lane >> 4) + j, n = 16 * nb + (lane & 15);
+        p.out[t] = (k < p.K && n < p.n_out) ? pack_src(p.src, n, k) : 0.f;
+    }
 }
 
 PackSrc plain_src(const float *W, int ldw, int rows)
@@ -3523,16 +3549,23 @@ tgm_status_t tgm::model_repack(tgm_model_t m, const ModelParams &w, hipStream_t 
         return TGM_EINVAL;
     const int M = m->M, D_e = m->D_e, D_t = m->D_t, D_x = m->D_x, MP = m->MB * 16;
     const int Dq = M + D_t, Dkv = M + D_e + D_t, KF = D_e + D_t;
+    RepackArgs ra{};
+    int blocks = 0;
+    auto pack = [&](const PackSrc &p, int n_out, int K, int KC, int NB, void *out) {
+        const int64_t total = (int64_t)KC * NB * kWave * 4;
+        if (total <= 0)
+            return;
+        ra.job[ra.n_jobs++] = PackJob{p, n_out, K, NB, blocks, total, (float *)out};
+        blocks += (int)cdiv(total, kPackPer);
+    };
     // GRU: one packed operand per gate, in gate order
     const int64_t gx = (int64_t)m->KXC * m->MB * kWave * 4, gh = (int64_t)m->KHC * m->MB * kWave * 4;
     for (int gte = 0; gte < 3; ++gte) {
-        TGM_TRY_STATUS(pack_launch(plain_src(w.W_ih + (int64_t)gte * M * D_x, D_x, M), M, D_x,
-                                   m->KXC, m->MB, (float *)m->gru_bx + gte * gx, s));
-        TGM_TRY_STATUS(pack_launch(plain_src(w.W_hh + (int64_t)gte * M * M, M, M), M, M, m->KHC,
-                                   m->MB, (float *)m->gru_bh + gte * gh, s));
+        pack(plain_src(w.W_ih + (int64_t)gte * M * D_x, D_x, M), M, D_x, m->KXC, m->MB,
+             (float *)m->gru_bx + gte * gx);
+        pack(plain_src(w.W_hh + (int64_t)gte * M * M, M, M), M, M, m->KHC, m->MB,
+             (float *)m->gru_bh + gte * gh);
     }
-    TGM_LAUNCH(k_pack_gru_bias, dim3((unsigned)cdiv(M, 128)), dim3(128), 0, s, M, MP, 3, w.b_ih,
-               w.b_hh, m->gru_bias);
     // node projections: rows of [W_q^s; W_k^s; W_v^s]
     {
         PackSrc p{};
@@ -3543,7 +3576,7 @@ tgm_status_t tgm::model_repack(tgm_model_t m, const ModelParams &w, hipStream_t 
         p.ldw[1] = p.ldw[2] = Dkv;
         p.rows = M;
         p.perm_Dt = -1;
-        TGM_TRY_STATUS(pack_launch(p, 3 * M, M, m->PC, m->PNB, m->proj_b, s));
+        pack(p, 3 * M, M, m->PC, m->PNB, m->proj_b);
     }
     // per-slot part of [K | V] in the slot-row column order [phi || efeat]
     PackSrc kv{};
@@ -3555,23 +3588,33 @@ tgm_status_t tgm::model_repack(tgm_model_t m, const ModelParams &w, hipStream_t 
     kv.perm_De = D_e;
     kv.perm_Dt = D_t;
     if (KF > 0)
-        TGM_TRY_STATUS(pack_launch(kv, 2 * M, KF, m->KFC, m->KVNB, m->kv_b, s));
+        pack(kv, 2 * M, KF, m->KFC, m->KVNB, m->kv_b);
     if ((m->fold || m->agg) && KF > 0) {
         PackSrc v = kv;
         v.W[0] = w.W_v;
-        TGM_TRY_STATUS(pack_launch(v, M, KF, m->KFC, m->VNB, m->v_b, s));
+        pack(v, M, KF, m->KFC, m->VNB, m->v_b);
         PackSrc u = kv;   // W_k^t [KF x M]: element (kf, d) = W_k[d][perm(kf)]
         u.trans = 1;
-        TGM_TRY_STATUS(pack_launch(u, KF, M, m->DC, m->KFC, m->uk_a, s));
+        pack(u, KF, M, m->DC, m->KFC, m->uk_a);
     }
-    TGM_TRY_STATUS(pack_launch(plain_src(w.W_o, 2 * M, M), M, 2 * M, m->OC, m->ONB, m->out_b, s));
-    // biases of the node projection: c_q = W_q^t phi(0) + b_q, then b_k, b_v
-    hipLaunchKernelGGL(k_fold_q_bias, dim3((unsigned)cdiv(M, 64)), dim3(64), 0, s, M, D_t, w.W_q,
-                       w.b_q, m->beta, m->pbias);
-    TGM_LAUNCHED();
-    TGM_LAUNCH(k_copy_f32, dim3((unsigned)cdiv(M, 128)), dim3(128), 0, s, w.b_k, m->pbias + M, M);
-    TGM_LAUNCH(k_copy_f32, dim3((unsigned)cdiv(M, 128)), dim3(128), 0, s, w.b_v,
-               m->pbias + 2 * M, M);
-    TGM_LAUNCH(k_copy_f32, dim3((unsigned)cdiv(M, 128)), dim3(128), 0, s, w.b_o, m->b_o, M);
+    pack(plain_src(w.W_o, 2 * M, M), M, 2 * M, m->OC, m->ONB, m->out_b);
+    // biases: c_q = W_q^t phi(0) + b_q of the node projection, then the rest
+    ra.cq0 = blocks;
+    ra.small0 = blocks + (int)cdiv(M, 4);
+    ra.M = M;
+    ra.MP = MP;
+    ra.D_t = D_t;
+    ra.b_ih = w.b_ih;
+    ra.b_hh = w.b_hh;
+    ra.W_q = w.W_q;
+    ra.b_q = w.b_q;
+    ra.b_k = w.b_k;
+    ra.b_v = w.b_v;
+    ra.b_o = w.b_o;
+    ra.beta = m->beta;
+    ra.gru_bias = m->gru_bias;
+    ra.pbias = m->pbias;
+    ra.out_bo = m->b_o;
+    TGM_LAUNCH(k_repack, dim3((unsigned)ra.small0 + 1), dim3(256), 0, s, ra);
     return TGM_OK;
 }
