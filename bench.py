@@ -407,32 +407,32 @@ def apan_work_model(wl, K, rows):
 
 def train_work_model(wl, rows):
     """Algorithmic flops per launch of the training step's GEMMs (k_gemm, all
-    shapes of one step averaged over its launches) and bytes of its
-    element-wise kernels.  Useful work only: valid slots (S), nodes with mail
-    (n_mail); the GEMMs also run over the empty slots and rows without mail,
-    which are zero."""
+    products of one step averaged over its launches) and bytes of the rows
+    launch.  Useful work only: roots (R), valid slots (S), nodes with mail
+    (n_mail); the attention's products run over (root, head) rows, a head's
+    d_h columns each, so H of them do the work of one M-wide product."""
     M, D_e, D_t, nb = wl.M, wl.D_e, wl.D_t, wl.nb
-    D_x, Dq, Dkv = wl.D_m + D_t, M + D_t, M + D_e + D_t
+    D_x, Dkv = wl.D_m + D_t, M + D_e + D_t
     n = len(rows)
     avg = lambda key: sum(r[key] for r in rows) / n
     S, R, n_mail, b = avg("slots"), avg("R"), avg("n_mail"), avg("b")
     f = 4
-    gemms = [  # (m, n, k) of every GEMM of one step
-        (b, M, M), (2 * b, M, M),                                  # predictor forward
-        (1, M, 2 * b), (1, 1, 2 * b), (1, M, b), (M, M, b), (M, M, 2 * b),
-        (b, M, M), (2 * b, M, M),                                  # predictor backward, dh
-        (R, M, Dq), (S, M, Dkv), (S, M, Dkv), (R, M, 2 * M),       # attention again
-        (M, 2 * M, R), (1, M, R), (R, 2 * M, M),                   # output projection
-        (M, Dkv, S), (M, Dkv, S), (1, M, S), (1, M, S), (M, Dq, R), (1, M, R),
-        (S, M, M), (S, M, M), (R, M, M),                           # dK, dV, dq; ds
+    gemms = [  # (m, n, k) of every product of one step
+        (b, M, M), (2 * b, M, M), (b, M, M), (2 * b, M, M),        # predictor, gradient of h
+        (M, M, b), (M, M, 2 * b), (1, M, 2 * b),
+        (R, M, M), (R, Dkv, M), (R, M, Dkv),                       # q, u, o
+        (R, 2 * M, M), (R, Dkv, M), (R, M, Dkv), (R, M, M),        # back: [o, s'], abar, q, s'
+        (M, M, R), (M, Dkv, R), (M, Dkv, R), (M, 2 * M, R),        # W_q, W_k, W_v, W_o
         (n_mail, 3 * M, D_x), (n_mail, 3 * M, M),                  # GRU gates again
-        (3 * M, D_x, n_mail), (3 * M, M, n_mail), (1, 3 * M, n_mail), (1, 3 * M, n_mail)]
+        (3 * M, D_x, n_mail), (3 * M, M, n_mail)]
     flops = sum(2.0 * m_ * n_ * k_ for m_, n_, k_ in gemms)
     byts = sum(f * (m_ * k_ + k_ * n_ + m_ * n_) for m_, n_, k_ in gemms)
-    L = len(gemms)
+    L = 8   # launches of one step
     return {"k_gemm": dict(flops=flops / L, bytes=byts / L),
-            "k_att_rows": dict(flops=0, bytes=R * Dq * f * 2 + S * Dkv * f * 2),
-            "k_adam": dict(flops=0, bytes=0)}
+            "k_att_fwd": dict(flops=4.0 * S * wl.H * Dkv, bytes=S * D_e * f + 2 * R * wl.H * Dkv * f),
+            "k_att_bwd": dict(flops=4.0 * S * wl.H * Dkv + 4.0 * S * wl.H * M,
+                              bytes=S * D_e * f + 2 * R * wl.H * Dkv * f + S * M * f),
+            "k_train_rows": dict(flops=0, bytes=2 * n_mail * (D_x + M) * f + 2 * R * M * f)}
 
 
 CSRC = ("common.h", "api.hip", "graph.hip", "state.hip", "model.hip", "runner.hip")

@@ -751,10 +751,24 @@ extern "C" tgm_status_t tgm_apan_step(tgm_apan_t a, tgm_graph_t g, int64_t iter,
         TGM_LAUNCH(k_apan_query_rows, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)),
                    dim3(256), 0, s, sb->n_nodes, cap, M, D_t, a->f_mem, a->omega, a->beta,
                    a->Xq);
-        TGM_TRY_STATUS(gemm_f32(false, true, cap, M, M + D_t, a->Xq, M + D_t, a->W_q, M + D_t,
-                                a->Q, M, a->b_q, false, s, sb->n_nodes));
-        TGM_TRY_STATUS(gemm_f32(false, false, cap, D_x, M, a->Q, M, a->W_k, D_x, a->U, D_x,
-                                nullptr, false, s, sb->n_nodes));
+        auto mul = [&](bool tb, int n, int k, const float *x, const float *w, int ldw, float *out,
+                       const float *bias) {   // rows of the node set only
+            GemmProb p;
+            p.m = cap;
+            p.n = n;
+            p.k = k;
+            p.A = x;
+            p.lda = k;
+            p.B = w;
+            p.ldb = ldw;
+            p.C = out;
+            p.ldc = n;
+            p.bias = bias;
+            p.live = sb->n_nodes;
+            return gemm_launch(false, tb, &p, 1, s);
+        };
+        TGM_TRY_STATUS(mul(true, M, M + D_t, a->Xq, a->W_q, M + D_t, a->Q, a->b_q));
+        TGM_TRY_STATUS(mul(false, D_x, M, a->Q, a->W_k, D_x, a->U, nullptr));
         TGM_LAUNCH(k_apan_qb, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)), dim3(256), 0, s,
                    sb->n_nodes, cap, M, a->Q, a->b_k, a->qb);
         AttnArgs2 aa{sb->n_nodes, cap, M, D_m, D_t, K, 1.f / sqrtf((float)M), a->U, a->qb,
@@ -763,10 +777,8 @@ extern "C" tgm_status_t tgm_apan_step(tgm_apan_t a, tgm_graph_t g, int64_t iter,
         TGM_LAUNCH(k_apan_attn, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)), dim3(256), 0, s,
                    aa);
         // the GRU on [aggregate || phi(t_newest - mem_ts)]
-        TGM_TRY_STATUS(gemm_f32(false, true, cap, 3 * M, D_x, a->X, D_x, a->W_ih, D_x, a->Gx,
-                                3 * M, a->b_ih, false, s, sb->n_nodes));
-        TGM_TRY_STATUS(gemm_f32(false, true, cap, 3 * M, M, a->f_mem, M, a->W_hh, M, a->Gh,
-                                3 * M, a->b_hh, false, s, sb->n_nodes));
+        TGM_TRY_STATUS(mul(true, 3 * M, D_x, a->X, a->W_ih, D_x, a->Gx, a->b_ih));
+        TGM_TRY_STATUS(mul(true, 3 * M, M, a->f_mem, a->W_hh, M, a->Gh, a->b_hh));
         TGM_LAUNCH(k_apan_gru, dim3((unsigned)cdiv((int64_t)cap * M, 256)), dim3(256), 0, s,
                    sb->n_nodes, cap, M, a->f_cnt, a->Gx, a->Gh, a->f_mem, mem_new);
         if (new_mem_ts)

@@ -915,13 +915,39 @@ struct ModelParams {
 };
 tgm_status_t model_repack(tgm_model_t m, const ModelParams &w, hipStream_t s);
 
-// C[m x n] = op(A) op(B) (+ bias[n]) (+ C when accumulate), fp32 MFMA, no
-// split of the reduction (the GEMM of the training step; op as there).  With
-// m_live (device, may be NULL) only the rows below min(m, *m_live) are
-// computed; the rest of C is left as it was.
-tgm_status_t gemm_f32(bool ta, bool tb, int m, int n, int k, const float *A, int lda,
-                      const float *B, int ldb, float *C, int ldc, const float *bias,
-                      bool accumulate, hipStream_t s, const int32_t *m_live = nullptr);
+// One product of a grouped GEMM launch (gemm_launch), row-major fp32:
+// C[m x n] = op(A)[m x k] op(B)[k x n], op(A)(i, kk) = ta ? A[kk lda + i] :
+// A[i lda + kk], op(B)(kk, j) = tb ? B[j ldb + kk] : B[kk ldb + j], `batch`
+// times with the given strides between the operands.  Then, in this order:
+// + bias[j]; with `gate`, 0 where gate[i ldg + j] is not positive; 0 in the columns below zero_cols of rows with row_on[i] <= 0;
+// + C when accumulate.  `live` (device): without ta, the rows at or past
+// *live are left as they were (whole tiles; a tile that holds the last live
+// row writes all its rows); with ta, the reduction ends there.  With ta the
+// reduction is cut into `splits` parts of equal length (a multiple of 32),
+// part z into C + z split_stride, to be added in order by the caller, and
+// with colsum the sums of op(A)'s rows go to colsum[z colsum_stride + i].
+// Nothing outside the m, n and k ranges is read.
+struct GemmProb {
+    const float *A = nullptr, *B = nullptr;
+    float *C = nullptr;
+    int m = 0, n = 0, k = 0, lda = 0, ldb = 0, ldc = 0;
+    const float *bias = nullptr;
+    const float *gate = nullptr;
+    int ldg = 0;
+    const int32_t *row_on = nullptr;
+    int zero_cols = 0;
+    int accumulate = 0;
+    const int32_t *live = nullptr;
+    int batch = 1;
+    int64_t sA = 0, sB = 0, sC = 0, sBias = 0;
+    int splits = 1;
+    int64_t split_stride = 0;
+    float *colsum = nullptr;
+    int64_t colsum_stride = 0, sColsum = 0;
+    int tile0 = 0, tiles_n = 0, tiles_m = 0, wide = 0;   // set by gemm_launch
+};
+constexpr int kGemmGroup = 12;   // products per launch
+tgm_status_t gemm_launch(bool ta, bool tb, const GemmProb *probs, int n, hipStream_t s);
 
 // The training step of one iteration (tgm_train_step) on stream s, from the
 // iteration's sample and fetch buffers, new memories and embeddings.

@@ -6,177 +6,41 @@
 // stage).
 //
 // Every reduction has a fixed order, so results are bit-reproducible: the
-// weight gradients are MFMA GEMMs whose long reduction dimension (slots,
-// roots, nodes) is split over workgroups into partial sums that a second
+// weight gradients are MFMA GEMMs whose long reduction dimension (roots,
+// nodes) is split over workgroups into partial sums that the optimizer's
 // launch adds in split order; the gradient of each node's updated memory
 // gathers its contributions (the roots and neighbour slots that read it)
-// after a radix sort of (node, contributor) keys.
+// after a stable radix sort by node.
+//
+// The attention's backward works on aggregates, as its forward does: with
+// a_s = [s'_u || efeat || phi] the row of slot s, q the root's query and per
+// head u = W_k^t q, the scores are a_s . u (b_k shifts every score of a head
+// alike, and a softmax ignores that), o = W_v abar + b_v with abar = sum_s
+// alpha_s a_s, and so
+//   dabar = W_v^t do, dalpha_s = a_s . dabar (b_v shifts them alike too),
+//   dscore_s = alpha_s (dalpha_s - sum alpha dalpha) / sqrt(d_h),
+//   du = sum_s dscore_s a_s, dq = W_k du, dW_k = sum q (x) du,
+//   dW_v = sum do (x) abar, ds'_u = dscore_s u + alpha_s dabar (memory part).
+// Every product then runs over (root, head) rows instead of slots: at a
+// batch of 4,000 (12,000 roots, 10 slots each, M = 100, 386-wide rows) 5.6
+// GFLOP instead of 46, and neither the slot rows (185 MB) nor their keys and
+// values are stored.  Two iterations of the training loop at that size took
+// 5.20 ms with products over slots and a launch (or two) per product, and
+// 1.81 ms with these, grouped eight launches to a step; one step at a batch
+// of 600: 919 and 229 us.
 #include <hip/hip_runtime.h>
 
 #include <hipcub/hipcub.hpp>
 
 #include <algorithm>
 #include <cmath>
+#include <utility>
 
 #include "common.h"
 
 using namespace tgm;
 
 namespace {
-
-// ------------------------------------------------------------------ GEMM
-// C[m x n] = op(A)[m x k] op(B)[k x n] (+ bias[n]) (+ C when accumulate),
-// row-major.  op(A)(i, kk) = ta ? A[kk lda + i] : A[i lda + kk];
-// op(B)(kk, j) = tb ? B[j ldb + kk] : B[kk ldb + j].  A workgroup of 4
-// wavefronts takes a 64 x 64 tile (32 x 32 per wavefront, v_mfma 16x16x4)
-// over the k range of its split (blockIdx.z); with several splits each
-// writes its partial tile to `part` and k_gemm_reduce adds them in order.
-// The k range goes in steps of kGK2 = 32 through two LDS buffers: the next
-// step's elements load into registers while the current step multiplies,
-// and one barrier per step hands the buffers over.  Within a split every
-// accumulator takes its k in increasing order, 16 at a time.
-constexpr int kGT = 64, kGK = 16, kGK2 = 32, kGPad = 4;
-constexpr int kMaxSplits = 64;
-
-struct GemmArgs {
-    int m, n, k;
-    const float *A;
-    int lda;
-    const float *B;
-    int ldb;
-    float *C;
-    int ldc;
-    const float *bias;
-    int accumulate;
-    int splits, kchunk;
-    float *part;
-    const int32_t *m_live;   // rows at or past *m_live are skipped (NULL: none)
-};
-
-// Element u of this thread's share of a 64 x kGK2 operand tile: (row, kk) of
-// the tile, laid out so that consecutive threads read consecutive addresses.
-template <bool T>
-__device__ __forceinline__ void gemm_elem(int tid, int u, int &r, int &kk)
-{
-    const int e = tid + u * 256;
-    if (T) {   // element (r, kk) at X[kk ld + r]: rows contiguous
-        r = e & (kGT - 1);
-        kk = e >> 6;
-    } else {   // element (r, kk) at X[r ld + kk]: k contiguous
-        r = e >> 5;
-        kk = e & (kGK2 - 1);
-    }
-}
-
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
-{
-    __shared__ __align__(16) float As[2][kGT][kGK2 + kGPad];
-    __shared__ __align__(16) float Bs[2][kGT][kGK2 + kGPad];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = blockIdx.y * kGT, n0 = blockIdx.x * kGT, z = blockIdx.z;
-    if (g.m_live && m0 >= *g.m_live)
-        return;   // the whole tile is past the live rows
-    const int k_lo = z * g.kchunk, k_hi = min(g.k, k_lo + g.kchunk);
-    const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-    const int q = lane >> 4, rl = lane & 15;
-    // the tile's elements of one k step, loaded branch-free (clamped
-    // addresses; the zero mask is applied where they are stored)
-    constexpr int NE = kGT * kGK2 / 256;
-    float ra[NE], rb[NE];
-    auto load = [&](int k0) {
-#pragma unroll
-        for (int u = 0; u < NE; ++u) {
-            int i, kk;
-            gemm_elem<TA>(tid, u, i, kk);
-            const int gi = min(m0 + i, g.m - 1), gk = min(k0 + kk, g.k - 1);
-            ra[u] = TA ? g.A[(int64_t)gk * g.lda + gi] : g.A[(int64_t)gi * g.lda + gk];
-            int j, kb;
-            gemm_elem<!TB>(tid, u, j, kb);
-            const int gj = min(n0 + j, g.n - 1), gkb = min(k0 + kb, g.k - 1);
-            rb[u] = TB ? g.B[(int64_t)gj * g.ldb + gkb] : g.B[(int64_t)gkb * g.ldb + gj];
-        }
-    };
-    auto store = [&](int k0, int buf) {
-#pragma unroll
-        for (int u = 0; u < NE; ++u) {
-            int i, kk;
-            gemm_elem<TA>(tid, u, i, kk);
-            As[buf][i][kk] = (m0 + i < g.m && k0 + kk < k_hi) ? ra[u] : 0.f;
-            int j, kb;
-            gemm_elem<!TB>(tid, u, j, kb);
-            Bs[buf][j][kb] = (n0 + j < g.n && k0 + kb < k_hi) ? rb[u] : 0.f;
-        }
-    };
-    f4 acc[2][2];
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-            acc[bi][bj] = f4{0.f, 0.f, 0.f, 0.f};
-    if (k_lo < k_hi) {
-        load(k_lo);
-        store(k_lo, 0);
-        __syncthreads();
-    }
-    int buf = 0;
-    for (int k0 = k_lo; k0 < k_hi; k0 += kGK2, buf ^= 1) {
-        const bool more = k0 + kGK2 < k_hi;
-        if (more)
-            load(k0 + kGK2);
-#pragma unroll
-        for (int h = 0; h < kGK2 / kGK; ++h) {
-#pragma unroll
-            for (int bi = 0; bi < 2; ++bi) {
-                const f4 a = *reinterpret_cast<const f4 *>(&As[buf][wr + bi * 16 + rl][16 * h + 4 * q]);
-#pragma unroll
-                for (int bj = 0; bj < 2; ++bj) {
-                    const f4 bv =
-                        *reinterpret_cast<const f4 *>(&Bs[buf][wc + bj * 16 + rl][16 * h + 4 * q]);
-                    acc[bi][bj] = mfma_k16(a, bv, acc[bi][bj]);
-                }
-            }
-        }
-        if (more) {
-            store(k0 + kGK2, buf ^ 1);
-            __syncthreads();
-        }
-    }
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = m0 + wr + bi * 16 + 4 * q + v, col = n0 + wc + bj * 16 + rl;
-                if (row >= g.m || col >= g.n)
-                    continue;
-                float x = acc[bi][bj][v];
-                if (g.splits > 1) {
-                    g.part[((int64_t)z * g.m + row) * g.n + col] = x;
-                } else {
-                    if (g.bias)
-                        x += g.bias[col];
-                    float *c = g.C + (int64_t)row * g.ldc + col;
-                    *c = g.accumulate ? *c + x : x;
-                }
-            }
-}
-
-__global__ __launch_bounds__(256) void k_gemm_reduce(GemmArgs g)
-{
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= (int64_t)g.m * g.n)
-        return;
-    const int row = (int)(t / g.n), col = (int)(t % g.n);
-    float x = 0.f;
-    for (int z = 0; z < g.splits; ++z)
-        x += g.part[((int64_t)z * g.m + row) * g.n + col];
-    if (g.bias)
-        x += g.bias[col];
-    float *c = g.C + (int64_t)row * g.ldc + col;
-    *c = g.accumulate ? *c + x : x;
-}
 
 // ------------------------------------------------------------- predictor
 // One wavefront per event e < b (lanes over the hidden units j < M <= 128):
@@ -239,86 +103,100 @@ __global__ __launch_bounds__(256) void k_pred(PredArgs a)
     }
 }
 
-// loss = (1/b) sum of the events' losses, in a fixed order (one workgroup)
-__global__ __launch_bounds__(256) void k_loss(const float *__restrict__ lossv, int b,
-                                              float *__restrict__ out)
-{
-    __shared__ float part[256];
-    float x = 0.f;
-    for (int e = threadIdx.x; e < b; e += 256)
-        x += lossv[e];
-    part[threadIdx.x] = x;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        *out = part[0] / (float)b;
-}
-
 // ------------------------------------------------------------- attention
-// Rows of the attention's inputs, one wavefront per row: Xq[r] = [s'_v ||
-// phi(0)] for the R roots, then kap[sl] = [s'_u || efeat[eid] || phi(t - t')]
-// for the R nb slots (zero for slots past the root's count).
+// What the step needs besides its products' outputs, one launch:
+//   root rows   Xo[r][M .. 2M) = s'_v (the query's and the output
+//               projection's input), one wavefront per root;
+//   node rows   X[p] = [mail || phi(mail_ts - mem_ts)] and Hm[p] = mem[p] of
+//               the node set's nodes with mail, zeros without, one wavefront
+//               per node;
+//   sort keys   contributor r < R is root r (it reads s' of node
+//               root_pos[r]), R + sl is slot sl (node nbr_pos[sl]); empty
+//               slots get the key cap, past every node;
+//   c_q         W_q phi(0) + b_q, one wavefront per unit.
 struct RowArgs {
-    int R, nb, M, D_e, D_t;
-    const int32_t *root_pos, *nbr_pos, *eid, *cnt;
-    const double *root_ts, *nts, *omega, *beta;
-    const float *s_new, *efeat;
-    float *Xq, *kap;
+    int R, nb, M, D_m, D_t, cap, ldx;
+    int n_root, n_node, n_key;   // workgroups of the first three parts
+    const int32_t *root_pos, *nbr_pos, *cnt, *n_nodes, *ver;
+    const double *mem_ts, *mail_ts, *omega, *beta;
+    const float *s_new, *mem, *mail, *W_q, *b_q;
+    float *Xo, *X, *Hm, *cq;
+    uint32_t *keys;
+    int32_t *vals;
 };
 
-__global__ __launch_bounds__(256) void k_att_rows(RowArgs a)
+__global__ __launch_bounds__(256) void k_train_rows(RowArgs a)
 {
-    const int64_t w = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    const int M = a.M, D_e = a.D_e, D_t = a.D_t;
-    if (w < a.R) {
-        const int r = (int)w;
-        float *x = a.Xq + (int64_t)r * (M + D_t);
-        const float *sv = a.s_new + (int64_t)a.root_pos[r] * M;
-        for (int k = lane; k < M; k += kWave)
-            x[k] = sv[k];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int M = a.M, D_m = a.D_m, D_t = a.D_t;
+    int blk = blockIdx.x;
+    if (blk < a.n_root) {
+        const int r = blk * 4 + wave;
+        if (r < a.R)
+            wave_copy_row(a.Xo + (int64_t)r * 2 * M + M, a.s_new + (int64_t)a.root_pos[r] * M, M,
+                          lane);
+        return;
+    }
+    blk -= a.n_root;
+    if (blk < a.n_node) {
+        const int p = blk * 4 + wave;
+        if (p >= min(*a.n_nodes, a.cap))
+            return;
+        float *x = a.X + (int64_t)p * a.ldx, *hm = a.Hm + (int64_t)p * M;
+        if (a.ver[p] < 0) {
+            for (int k = lane; k < D_m + D_t; k += kWave)
+                x[k] = 0.f;
+            for (int k = lane; k < M; k += kWave)
+                hm[k] = 0.f;
+            return;
+        }
+        const double dt = a.mail_ts[p] - a.mem_ts[p];
+        wave_copy_2rows(hm, a.mem + (int64_t)p * M, M, x, a.mail + (int64_t)p * D_m, D_m, lane);
         for (int d = lane; d < D_t; d += kWave)
-            x[M + d] = time_enc(a.omega[d], a.beta[d], 0.0);
+            x[D_m + d] = time_enc(a.omega[d], a.beta[d], dt);
         return;
     }
-    const int64_t sl = w - a.R;
-    if (sl >= (int64_t)a.R * a.nb)
-        return;
-    const int r = (int)(sl / a.nb), j = (int)(sl % a.nb);
-    const int Dkv = M + D_e + D_t;
-    float *x = a.kap + sl * Dkv;
-    if (j >= a.cnt[r]) {
-        for (int k = lane; k < Dkv; k += kWave)
-            x[k] = 0.f;
+    blk -= a.n_node;
+    if (blk < a.n_key) {
+        const int64_t t = (int64_t)blk * 256 + threadIdx.x;
+        const int64_t S = (int64_t)a.R * a.nb;
+        if (t >= a.R + S)
+            return;
+        uint32_t key;
+        if (t < a.R) {
+            key = (uint32_t)a.root_pos[t];
+        } else {
+            const int64_t sl = t - a.R;
+            const int r = (int)(sl / a.nb), j = (int)(sl % a.nb);
+            key = j < a.cnt[r] ? (uint32_t)a.nbr_pos[sl] : (uint32_t)a.cap;
+        }
+        a.keys[t] = min(key, (uint32_t)a.cap);
+        a.vals[t] = (int32_t)t;
         return;
     }
-    const float *su = a.s_new + (int64_t)a.nbr_pos[sl] * M;
-    const float *f = a.efeat + (int64_t)a.eid[sl] * D_e;
-    const double dt = a.root_ts[r] - a.nts[sl];
-    for (int k = lane; k < M; k += kWave)
-        x[k] = su[k];
-    for (int k = lane; k < D_e; k += kWave)
-        x[M + k] = f[k];
+    blk -= a.n_key;
+    const int k = blk * 4 + wave;
+    if (k >= M)
+        return;
+    float acc = 0.f;
     for (int d = lane; d < D_t; d += kWave)
-        x[M + D_e + d] = time_enc(a.omega[d], a.beta[d], dt);
+        acc += a.W_q[(int64_t)k * (M + D_t) + M + d] * time_enc(a.omega[d], a.beta[d], 0.0);
+    acc = wave_sum(acc);
+    if (lane == 0)
+        a.cq[k] = acc + a.b_q[k];
 }
 
-// One wavefront per root: the scores of each head over the root's valid
-// slots, their softmax (alpha [R x H x nb]) and a = sum_j alpha_j V_j into
-// Xo[:, 0:M]; Xo[:, M:2M] = s'_v.  Lanes hold the output dims k = lane,
-// lane + 64 (M <= 128).
-struct CoreArgs {
-    int R, nb, M, H;
-    float scale;
-    const int32_t *cnt, *root_pos;
-    const float *Q, *KV, *s_new, *dXo;   // [R x M], [R nb x 2M], [cap x M], [R x 2M]
-    float *alpha, *Xo;                   // [R x H x nb], [R x 2M]
-    float *dKV, *dQ;                     // [R nb x 2M], [R x M]
-};
+// Sum over the wavefront, the same value in every lane: the 16-lane rows with
+// DPP moves, then the four row sums through scalar registers (no LDS).
+__device__ __forceinline__ float wave_total(float v)
+{
+    const int x = __float_as_int(row16_sum(v));
+    const float a = __int_as_float(__builtin_amdgcn_readlane(x, 0)) +
+                    __int_as_float(__builtin_amdgcn_readlane(x, 16));
+    const float b = __int_as_float(__builtin_amdgcn_readlane(x, 32)) +
+                    __int_as_float(__builtin_amdgcn_readlane(x, 48));
+    return a + b;
+}
 
 __device__ __forceinline__ float wave_max(float v)
 {
@@ -328,343 +206,422 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
-__global__ __launch_bounds__(256) void k_att_core(CoreArgs a)
+__device__ __forceinline__ float lane_of(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+struct AttArgs {
+    int R, nb, M, D_e, D_t, H, ldu;
+    float scale;
+    const int32_t *cnt, *root_pos, *nbr_pos, *eid;
+    const double *root_ts, *nts, *omega, *beta;
+    const float *s_new, *efeat, *U;   // U [R x H x ldu]
+    float *alpha;                     // [R x H x nb]
+    float *abar;                      // forward: sum_s alpha_s a_s [R x H x ldu]
+    float *dbar;                      // backward: dabar in, du out [R x H x ldu]
+    float *dKm;                       // backward: [R nb x M], filled slots only
+};
+
+// A row [s' || efeat || phi] in a wavefront's registers: lane l holds columns
+// l + 64 i of each part, zero past the part's width (CE, CT: 64-wide groups
+// of the edge features and time codes; M <= 128).
+template <int CE, int CT>
+struct Row {
+    float m[2], e[CE], t[CT];
+
+    __device__ __forceinline__ void load_cols(const float *x, const AttArgs &a, int lane)
+    {
+        const int M = a.M, D_e = a.D_e, D_t = a.D_t;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            m[i] = x[min(lane + kWave * i, M - 1)];
+#pragma unroll
+        for (int i = 0; i < CE; ++i)
+            e[i] = D_e > 0 ? x[M + min(lane + kWave * i, D_e - 1)] : 0.f;
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+            t[i] = D_t > 0 ? x[M + D_e + min(lane + kWave * i, D_t - 1)] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            m[i] = lane + kWave * i < M ? m[i] : 0.f;
+#pragma unroll
+        for (int i = 0; i < CE; ++i)
+            e[i] = lane + kWave * i < D_e ? e[i] : 0.f;
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+            t[i] = lane + kWave * i < D_t ? t[i] : 0.f;
+    }
+    __device__ __forceinline__ void store_cols(float *x, const AttArgs &a, int lane) const
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (lane + kWave * i < a.M)
+                x[lane + kWave * i] = m[i];
+#pragma unroll
+        for (int i = 0; i < CE; ++i)
+            if (lane + kWave * i < a.D_e)
+                x[a.M + lane + kWave * i] = e[i];
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+            if (lane + kWave * i < a.D_t)
+                x[a.M + a.D_e + lane + kWave * i] = t[i];
+    }
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            m[i] = 0.f;
+#pragma unroll
+        for (int i = 0; i < CE; ++i)
+            e[i] = 0.f;
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+            t[i] = 0.f;
+    }
+    __device__ __forceinline__ float dot(const Row &o) const   // this lane's part
+    {
+        float p = 0.f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            p = fmaf(m[i], o.m[i], p);
+#pragma unroll
+        for (int i = 0; i < CE; ++i)
+            p = fmaf(e[i], o.e[i], p);
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+            p = fmaf(t[i], o.t[i], p);
+        return p;
+    }
+    __device__ __forceinline__ void axpy(float w, const Row &o)
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            m[i] = fmaf(w, o.m[i], m[i]);
+#pragma unroll
+        for (int i = 0; i < CE; ++i)
+            e[i] = fmaf(w, o.e[i], e[i]);
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+            t[i] = fmaf(w, o.t[i], t[i]);
+    }
+};
+
+// The rows of up to NC slots of a root, every load issued before the time
+// codes are computed.
+template <int CE, int CT, int NC>
+struct SlotRows {
+    Row<CE, CT> x[NC];
+
+    __device__ __forceinline__ void load(const AttArgs &a, int r, int j0, int nj, int lane)
+    {
+        const int64_t sl = (int64_t)r * a.nb + j0 + min(lane, nj - 1);
+        const int32_t pos = a.nbr_pos[sl], ev = a.eid[sl];
+        const double dt = a.root_ts[r] - a.nts[sl];
+        const int M = a.M, D_e = a.D_e, D_t = a.D_t;
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            const int jj = min(j, nj - 1);
+            const float *s = a.s_new + (int64_t)__builtin_amdgcn_readlane(pos, jj) * M;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                x[j].m[i] = s[min(lane + kWave * i, M - 1)];
+            if (D_e > 0) {
+                const float *f = a.efeat + (int64_t)__builtin_amdgcn_readlane(ev, jj) * D_e;
+#pragma unroll
+                for (int i = 0; i < CE; ++i)
+                    x[j].e[i] = f[min(lane + kWave * i, D_e - 1)];
+            } else {
+#pragma unroll
+                for (int i = 0; i < CE; ++i)
+                    x[j].e[i] = 0.f;
+            }
+        }
+        const long long dti = __double_as_longlong(dt);
+        const int lo = (int)dti, hi = (int)(dti >> 32);
+#pragma unroll
+        for (int i = 0; i < CT; ++i) {
+            if (kWave * i >= D_t) {
+#pragma unroll
+                for (int j = 0; j < NC; ++j)
+                    x[j].t[i] = 0.f;
+                continue;
+            }
+            const int d = min(lane + kWave * i, D_t - 1);
+            const double om = a.omega[d], be = a.beta[d];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                const int jj = min(j, nj - 1);
+                const unsigned l = (unsigned)__builtin_amdgcn_readlane(lo, jj);
+                const long long h = __builtin_amdgcn_readlane(hi, jj);
+                x[j].t[i] = time_enc(om, be, __longlong_as_double((h << 32) | l));
+            }
+        }
+    }
+};
+
+// Forward values again, one wavefront per root: per head the scores of the
+// root's slots, their softmax alpha and abar = sum_s alpha_s a_s.  Roots with
+// up to NC slots keep their rows in registers for every head and both passes;
+// longer ones read them again.  Bound by the vector ALUs: the time codes, the
+// two dot products and the weighted sums of every slot.
+template <int CE, int CT, int NC>
+__global__ __launch_bounds__(256) void k_att_fwd(AttArgs a)
 {
     const int r = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
     if (r >= a.R)
         return;
-    const int M = a.M, H = a.H, nb = a.nb, dh = M / H, cr = a.cnt[r];
-    float q[2], acc[2] = {0.f, 0.f};
-    int head[2];
+    const int cr = __builtin_amdgcn_readfirstlane(a.cnt[r]);
+    SlotRows<CE, CT, NC> rows;
+    if (cr > 0 && cr <= NC)
+        rows.load(a, r, 0, cr, lane);
+    for (int eta = 0; eta < a.H; ++eta) {
+        const int64_t o = ((int64_t)r * a.H + eta) * a.ldu;
+        Row<CE, CT> acc;
+        acc.clear();
+        if (cr > 0) {
+            Row<CE, CT> u;
+            u.load_cols(a.U + o, a, lane);
+            float mine = -INFINITY;   // lane j < cr: the score of slot j
+            for (int j0 = 0; j0 < cr; j0 += NC) {
+                const int nj = min(NC, cr - j0);
+                if (cr > NC)
+                    rows.load(a, r, j0, nj, lane);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int k = lane + 64 * u;
-        q[u] = k < M ? a.Q[(int64_t)r * M + k] : 0.f;
-        head[u] = k < M ? k / dh : -1;
-    }
-    for (int eta = 0; eta < H && cr > 0; ++eta) {
-        float mine = -INFINITY;   // lane j < cr: the score of slot j
-        for (int j = 0; j < cr; ++j) {
-            const float *K = a.KV + ((int64_t)r * nb + j) * 2 * M;
-            float p = 0.f;
+                for (int j = 0; j < NC; ++j)
+                    if (j < nj) {
+                        const float sc = wave_total(rows.x[j].dot(u)) * a.scale;
+                        mine = lane == j0 + j ? sc : mine;
+                    }
+            }
+            const float mx = wave_max(mine);
+            const float ex = lane < cr ? expf(mine - mx) : 0.f;
+            const float al = ex / wave_total(ex);
+            if (lane < cr)
+                a.alpha[((int64_t)r * a.H + eta) * a.nb + lane] = al;
+            for (int j0 = 0; j0 < cr; j0 += NC) {
+                const int nj = min(NC, cr - j0);
+                if (cr > NC)
+                    rows.load(a, r, j0, nj, lane);
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (head[u] == eta)
-                    p += q[u] * K[lane + 64 * u];
-            const float sc = wave_sum(p) * a.scale;
-            if (lane == j)
-                mine = sc;
+                for (int j = 0; j < NC; ++j)
+                    if (j < nj)
+                        acc.axpy(lane_of(al, j0 + j), rows.x[j]);
+            }
         }
-        const float mx = wave_max(mine);
-        const float ex = lane < cr ? expf(mine - mx) : 0.f;
-        const float al = ex / wave_sum(ex);
-        if (lane < cr)
-            a.alpha[((int64_t)r * H + eta) * nb + lane] = al;
-        for (int j = 0; j < cr; ++j) {
-            const float alj = __shfl(al, j, kWave);
-            const float *V = a.KV + ((int64_t)r * nb + j) * 2 * M + M;
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (head[u] == eta)
-                    acc[u] += alj * V[lane + 64 * u];
-        }
-    }
-    const float *sv = a.s_new + (int64_t)a.root_pos[r] * M;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int k = lane + 64 * u;
-        if (k < M) {
-            a.Xo[(int64_t)r * 2 * M + k] = acc[u];
-            a.Xo[(int64_t)r * 2 * M + M + k] = sv[k];
-        }
+        acc.store_cols(a.abar + o, a, lane);
     }
 }
 
-// Backward of the core, one wavefront per root: with da = dXo[:, 0:M],
-// dalpha_j = da . V_j (per head), dscore_j = alpha_j (dalpha_j - sum alpha
-// dalpha), dV_j = alpha_j da, dK_j = dscore_j q scale, dq = sum_j dscore_j K_j
-// scale.  Slots past the count get zero rows.
-__global__ __launch_bounds__(256) void k_att_core_bwd(CoreArgs a)
+// Backward, one wavefront per root and the same layout: per head dalpha_s =
+// a_s . dabar, the scores' gradients, du = sum_s dscore_s a_s (in place of
+// dabar) and each slot's gradient of s'_u, summed over the heads.
+template <int CE, int CT, int NC>
+__global__ __launch_bounds__(256) void k_att_bwd(AttArgs a)
 {
     const int r = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
     if (r >= a.R)
         return;
-    const int M = a.M, H = a.H, nb = a.nb, dh = M / H, cr = a.cnt[r];
-    float q[2], da[2], dq[2] = {0.f, 0.f};
-    int head[2];
+    const int cr = __builtin_amdgcn_readfirstlane(a.cnt[r]), M = a.M;
+    SlotRows<CE, CT, NC> rows;
+    if (cr > 0 && cr <= NC)
+        rows.load(a, r, 0, cr, lane);
+    float dk[NC][2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int k = lane + 64 * u;
-        q[u] = k < M ? a.Q[(int64_t)r * M + k] : 0.f;
-        da[u] = k < M ? a.dXo[(int64_t)r * 2 * M + k] : 0.f;
-        head[u] = k < M ? k / dh : -1;
-    }
-    for (int eta = 0; eta < H && cr > 0; ++eta) {
-        const float *al = a.alpha + ((int64_t)r * H + eta) * nb;
-        float sdot = 0.f;
-        for (int j = 0; j < cr; ++j) {
-            const float *V = a.KV + ((int64_t)r * nb + j) * 2 * M + M;
-            float p = 0.f;
+    for (int j = 0; j < NC; ++j)
+        dk[j][0] = dk[j][1] = 0.f;
+    for (int eta = 0; eta < a.H; ++eta) {
+        const int64_t o = ((int64_t)r * a.H + eta) * a.ldu;
+        Row<CE, CT> acc;
+        acc.clear();
+        if (cr > 0) {
+            Row<CE, CT> db;
+            db.load_cols(a.dbar + o, a, lane);
+            float um[2];
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (head[u] == eta)
-                    p += da[u] * V[lane + 64 * u];
-            sdot += al[j] * wave_sum(p);
+            for (int i = 0; i < 2; ++i)
+                um[i] = a.U[o + min(lane + kWave * i, M - 1)];
+            const float al = lane < cr ? a.alpha[((int64_t)r * a.H + eta) * a.nb + lane] : 0.f;
+            float da = 0.f;   // lane j < cr: dalpha of slot j
+            for (int j0 = 0; j0 < cr; j0 += NC) {
+                const int nj = min(NC, cr - j0);
+                if (cr > NC)
+                    rows.load(a, r, j0, nj, lane);
+#pragma unroll
+                for (int j = 0; j < NC; ++j)
+                    if (j < nj) {
+                        const float d = wave_total(rows.x[j].dot(db));
+                        da = lane == j0 + j ? d : da;
+                    }
+            }
+            const float dsc = al * (da - wave_total(al * da)) * a.scale;
+            for (int j0 = 0; j0 < cr; j0 += NC) {
+                const int nj = min(NC, cr - j0);
+                if (cr > NC)
+                    rows.load(a, r, j0, nj, lane);
+#pragma unroll
+                for (int j = 0; j < NC; ++j)
+                    if (j < nj) {
+                        const float w = lane_of(dsc, j0 + j), aj = lane_of(al, j0 + j);
+                        acc.axpy(w, rows.x[j]);
+                        float g[2];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            g[i] = w * um[i] + aj * db.m[i];
+                        if (cr <= NC) {
+                            dk[j][0] += g[0];
+                            dk[j][1] += g[1];
+                        } else {   // the heads' sum in memory
+                            float *x = a.dKm + ((int64_t)r * a.nb + j0 + j) * M;
+#pragma unroll
+                            for (int i = 0; i < 2; ++i)
+                                if (lane + kWave * i < M)
+                                    x[lane + kWave * i] =
+                                        g[i] + (eta > 0 ? x[lane + kWave * i] : 0.f);
+                        }
+                    }
+            }
         }
-        for (int j = 0; j < cr; ++j) {
-            const float *K = a.KV + ((int64_t)r * nb + j) * 2 * M;
-            const float *V = K + M;
-            float p = 0.f;
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (head[u] == eta)
-                    p += da[u] * V[lane + 64 * u];
-            const float dal = wave_sum(p);
-            const float dsc = al[j] * (dal - sdot) * a.scale;
-            float *dK = a.dKV + ((int64_t)r * nb + j) * 2 * M;
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (head[u] == eta) {
-                    const int k = lane + 64 * u;
-                    dK[k] = dsc * q[u];
-                    dK[M + k] = al[j] * da[u];
-                    dq[u] += dsc * K[k];
-                }
-        }
+        acc.store_cols(a.dbar + o, a, lane);
     }
-    for (int j = cr; j < nb; ++j) {
-        float *dK = a.dKV + ((int64_t)r * nb + j) * 2 * M;
-        for (int k = lane; k < 2 * M; k += kWave)
-            dK[k] = 0.f;
-    }
-    if (cr == 0)
-        for (int j = 0; j < nb; ++j) {
-            float *dK = a.dKV + ((int64_t)r * nb + j) * 2 * M;
-            for (int k = lane; k < 2 * M; k += kWave)
-                dK[k] = 0.f;
-        }
+    if (cr <= NC)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int k = lane + 64 * u;
-        if (k < M)
-            a.dQ[(int64_t)r * M + k] = dq[u];
-    }
-}
-
-// dst = src where gate > 0, else 0 (the ReLU of the output projection)
-__global__ __launch_bounds__(256) void k_relu_mask(const float *__restrict__ src,
-                                                   const float *__restrict__ gate,
-                                                   float *__restrict__ dst, int64_t n)
-{
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t < n)
-        dst[t] = gate[t] > 0.f ? src[t] : 0.f;
+        for (int j = 0; j < NC; ++j)
+            if (j < cr)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (lane + kWave * i < M)
+                        a.dKm[((int64_t)r * a.nb + j) * M + lane + kWave * i] = dk[j][i];
 }
 
 // ------------------------------------------- gradient of the new memories
-// Keys (node << 32) | contributor: contributor r < R is root r (it reads s'
-// of node root_pos[r]), R + sl is slot sl (node nbr_pos[sl]); empty slots get
-// the largest key.
-__global__ __launch_bounds__(256) void k_ds_keys(int R, int nb, const int32_t *__restrict__ root_pos,
-                                                 const int32_t *__restrict__ nbr_pos,
-                                                 const int32_t *__restrict__ cnt,
-                                                 uint64_t *__restrict__ keys)
-{
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t S = (int64_t)R * nb;
-    if (t >= R + S)
-        return;
-    uint64_t key;
-    if (t < R) {
-        key = ((uint64_t)(uint32_t)root_pos[t] << 32) | (uint64_t)t;
-    } else {
-        const int64_t sl = t - R;
-        const int r = (int)(sl / nb), j = (int)(sl % nb);
-        key = j < cnt[r] ? ((uint64_t)(uint32_t)nbr_pos[sl] << 32) | (uint64_t)t : ~(uint64_t)0;
-    }
-    keys[t] = key;
-}
+// The contributors sorted by node (a stable sort, so in contributor order
+// within a node) are summed in blocks of 64 sorted positions, one wavefront
+// each: a node's run that lies inside a block is finished there; the part of
+// a run that began in an earlier block goes to head[block], and the start of
+// a run that goes on past the block to tail[block].  k_ds_join then adds the
+// open runs, block by block, so a hub's thousands of contributors spread over
+// many wavefronts.  ds[p] is the sum of dXo[r][M .. 2M) over its roots and of
+// dKm[sl] over its slots; every node of the node set has a contributor.
+constexpr int kDsBatch = 8;   // rows in flight
 
-// Segment bounds of the sorted keys: seg[p] .. seg_end[p] hold node p's
-// contributors, in contributor order.
-__global__ __launch_bounds__(256) void k_ds_bounds(int64_t n, const uint64_t *__restrict__ keys,
-                                                   int32_t cap, int32_t *__restrict__ seg,
-                                                   int32_t *__restrict__ seg_end)
+__global__ __launch_bounds__(256) void k_ds_block(int64_t n_items, int32_t cap, int M, int R,
+                                                  const uint32_t *__restrict__ keys,
+                                                  const int32_t *__restrict__ vals,
+                                                  const float *__restrict__ dXo,
+                                                  const float *__restrict__ dKm,
+                                                  float *__restrict__ ds,
+                                                  float *__restrict__ head,
+                                                  float *__restrict__ tail)
 {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n)
-        return;
-    const uint64_t k = keys[i];
-    if (k == ~(uint64_t)0)
-        return;
-    const int32_t p = (int32_t)(k >> 32);
-    if (p < 0 || p >= cap)
-        return;
-    if (i == 0 || (keys[i - 1] >> 32) != (k >> 32))
-        seg[p] = (int32_t)i;
-    if (i == n - 1 || (keys[i + 1] >> 32) != (k >> 32))
-        seg_end[p] = (int32_t)(i + 1);
-}
-
-// The sum runs in fixed chunks of kDsChunk contributors so that nodes with
-// many contributors (hubs) spread over many wavefronts.  k_ds_chunks counts
-// each node's chunks and scans the counts (one workgroup: chunk_off[p] is the
-// first chunk of node p, chunk_off[cap] the total); k_ds_partial sums one
-// chunk per wavefront iteration (a grid-stride loop over the chunks); k_ds
-// adds each node's chunk sums in order.  ds[p] is, in contributor order, the
-// sum of dXq[r] + dXo[r][M:2M] over its roots and of dKm[sl] over its slots.
-constexpr int kDsChunk = 64;
-constexpr int kDsScanThreads = 1024;
-
-__global__ __launch_bounds__(kDsScanThreads) void k_ds_chunks(const int32_t *__restrict__ n_nodes,
-                                                              int32_t cap,
-                                                              const int32_t *__restrict__ seg,
-                                                              const int32_t *__restrict__ seg_end,
-                                                              int32_t *__restrict__ chunk_off)
-{
-    __shared__ int32_t s_sum[kDsScanThreads];
-    const int n = min(*n_nodes, cap), tid = threadIdx.x;
-    // each thread takes a contiguous run of nodes
-    const int per = (cap + kDsScanThreads - 1) / kDsScanThreads;
-    const int p0 = tid * per, p1 = min(cap, p0 + per);
-    auto chunks = [&](int p) {
-        return p < n ? (max(seg_end[p] - seg[p], 0) + kDsChunk - 1) / kDsChunk : 0;
-    };
-    int32_t local = 0;
-    for (int p = p0; p < p1; ++p)
-        local += chunks(p);
-    s_sum[tid] = local;
-    __syncthreads();
-    for (int o = 1; o < kDsScanThreads; o <<= 1) {   // inclusive scan (Hillis-Steele)
-        const int32_t v = tid >= o ? s_sum[tid - o] : 0;
-        __syncthreads();
-        s_sum[tid] += v;
-        __syncthreads();
-    }
-    int32_t run = s_sum[tid] - local;
-    for (int p = p0; p < p1; ++p) {
-        chunk_off[p] = run;
-        run += chunks(p);
-    }
-    if (tid == kDsScanThreads - 1)
-        chunk_off[cap] = s_sum[tid];
-}
-
-__global__ __launch_bounds__(256) void k_ds_partial(int32_t cap, int M, int R, int64_t n_items,
-                                                    const uint64_t *__restrict__ keys,
-                                                    const int32_t *__restrict__ seg,
-                                                    const int32_t *__restrict__ seg_end,
-                                                    const int32_t *__restrict__ chunk_off,
-                                                    const float *__restrict__ dXq,
-                                                    const float *__restrict__ dXo,
-                                                    const float *__restrict__ dKm,
-                                                    float *__restrict__ part)
-{
+    const int64_t blk = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int32_t total = chunk_off[cap];
-    for (int64_t t = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6; t < total; t += nw) {
-        int lo = 0, hi = cap;   // the node p with chunk_off[p] <= t < chunk_off[p + 1]
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (chunk_off[mid] <= t)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        const int p = lo;
-        const int64_t i0 = max((int64_t)seg[p], (int64_t)0) + (t - chunk_off[p]) * kDsChunk;
-        const int64_t i1 = min(min((int64_t)seg_end[p], i0 + kDsChunk), n_items);
-        float acc[2] = {0.f, 0.f};
-        for (int64_t i = i0; i < i1; ++i) {
-            const int64_t c = (int64_t)(keys[i] & 0xffffffffu);
-            if (c >= n_items)
-                continue;
+    const int64_t i0 = blk * kWave;
+    if (i0 >= n_items)
+        return;
+    const int64_t i = min(i0 + lane, n_items - 1);
+    const bool in = i0 + lane < n_items;
+    const uint32_t key = in ? keys[i] : (uint32_t)cap;
+    const int32_t val = vals[i];
+    const uint32_t before = i0 > 0 ? keys[i0 - 1] : ~0u;
+    const uint32_t after = i0 + kWave < n_items ? keys[i0 + kWave] : ~0u;
+    const uint32_t up = (uint32_t)__shfl_up((int)key, 1, kWave);   // every lane active
+    const uint32_t down = (uint32_t)__shfl_down((int)key, 1, kWave);
+    const uint32_t prev = lane > 0 ? up : before, next = lane < 63 ? down : after;
+    const uint64_t live = __ballot(key < (uint32_t)cap);
+    if (live == 0)
+        return;
+    const int n = 64 - __clzll(live);   // the empty slots sort last
+    const uint64_t starts = __ballot(key != prev), ends = __ballot(key != next);
+    const int c0 = min(lane, M - 1), c1 = min(lane + kWave, M - 1);
+    float a0 = 0.f, a1 = 0.f;
+    bool open = true;   // the run began before this block
+    for (int b = 0; b < n; b += kDsBatch) {
+        float x[kDsBatch][2];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int k = lane + 64 * u;
-                if (k >= M)
-                    continue;
-                acc[u] += c < R ? dXq[c * M + k] + dXo[c * 2 * M + M + k]
-                                : dKm[(c - R) * M + k];
+        for (int u = 0; u < kDsBatch; ++u) {
+            const int c = __builtin_amdgcn_readlane(val, min(b + u, n - 1));
+            const float *row = c < R ? dXo + (int64_t)c * 2 * M + M
+                                     : dKm + (int64_t)(c - R) * M;
+            x[u][0] = row[c0];
+            x[u][1] = row[c1];
+        }
+#pragma unroll
+        for (int u = 0; u < kDsBatch; ++u) {
+            const int k = b + u;
+            if (k >= n)
+                break;
+            if ((starts >> k) & 1) {
+                a0 = a1 = 0.f;
+                open = false;
+            }
+            a0 += x[u][0];
+            a1 += x[u][1];
+            const bool end = (ends >> k) & 1;
+            if (end || k == 63) {
+                float *o = open ? head + blk * M
+                                : end ? ds + (int64_t)__builtin_amdgcn_readlane((int)key, k) * M
+                                      : tail + blk * M;
+                if (lane < M)
+                    o[lane] = a0;
+                if (lane + kWave < M)
+                    o[lane + kWave] = a1;
             }
         }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int k = lane + 64 * u;
-            if (k < M)
-                part[t * M + k] = acc[u];
-        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_ds(const int32_t *__restrict__ n_nodes, int32_t cap,
-                                            int M, const int32_t *__restrict__ chunk_off,
-                                            const float *__restrict__ part, float *__restrict__ ds)
+// One wavefront per block whose last run goes on: tail[block], then the heads
+// of the blocks the run reaches, in order.
+__global__ __launch_bounds__(256) void k_ds_join(int64_t n_items, int32_t cap, int M,
+                                                 const uint32_t *__restrict__ keys,
+                                                 const float *__restrict__ head,
+                                                 const float *__restrict__ tail,
+                                                 float *__restrict__ ds)
 {
-    const int p = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
+    const int64_t blk = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
-    if (p >= cap)
+    const int64_t last = blk * kWave + kWave - 1;
+    if (last + 1 >= n_items)
         return;
-    const int n = min(*n_nodes, cap);
-    float acc[2] = {0.f, 0.f};
-    if (p < n)
-        for (int32_t t = chunk_off[p]; t < chunk_off[p + 1]; ++t)
+    const uint32_t p = keys[last];
+    if (p >= (uint32_t)cap || keys[last + 1] != p ||
+        (keys[blk * kWave] == p && blk > 0 && keys[blk * kWave - 1] == p))
+        return;   // no run goes on, or it began in an earlier block
+    const int c0 = min(lane, M - 1), c1 = min(lane + kWave, M - 1);
+    float a0 = tail[blk * M + c0], a1 = tail[blk * M + c1];
+    // how many blocks follow: their first keys, 64 at a time
+    for (int64_t f = blk + 1;; f += kWave) {
+        const int64_t at = (f + lane) * kWave;
+        const uint64_t same = __ballot(at < n_items && keys[min(at, n_items - 1)] == p);
+        const int n = ~same == 0 ? 64 : __ffsll((long long)~same) - 1;
+        for (int b = 0; b < n; b += kDsBatch) {
+            float x[kDsBatch][2];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int k = lane + 64 * u;
-                if (k < M)
-                    acc[u] += part[(int64_t)t * M + k];
+            for (int u = 0; u < kDsBatch; ++u) {
+                const float *row = head + (f + min(b + u, n - 1)) * M;
+                x[u][0] = row[c0];
+                x[u][1] = row[c1];
             }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int k = lane + 64 * u;
-        if (k < M)
-            ds[(int64_t)p * M + k] = acc[u];
+            for (int u = 0; u < kDsBatch; ++u)
+                if (b + u < n) {
+                    a0 += x[u][0];
+                    a1 += x[u][1];
+                }
+        }
+        if (n < kWave)
+            break;
     }
+    if (lane < M)
+        ds[(int64_t)p * M + lane] = a0;
+    if (lane + kWave < M)
+        ds[(int64_t)p * M + lane + kWave] = a1;
 }
 
 // ------------------------------------------------------------------- GRU
-// Rows of the memory updater's inputs: X[p] = [mail || phi(mail_ts - mem_ts)]
-// and Hm[p] = mem[p] for nodes with mail (p < n_nodes, ver >= 0), zero rows
-// for the others (up to cap), one wavefront per row.
-struct GruRowArgs {
-    const int32_t *n_nodes;
-    int cap, M, D_m, D_t;
-    const float *mem, *mail;
-    const double *mem_ts, *mail_ts, *omega, *beta;
-    const int32_t *ver;
-    float *X, *Hm;
-};
-
-__global__ __launch_bounds__(256) void k_gru_rows(GruRowArgs a)
-{
-    const int p = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    if (p >= a.cap)
-        return;
-    const int M = a.M, D_m = a.D_m, D_t = a.D_t, D_x = D_m + D_t;
-    float *x = a.X + (int64_t)p * D_x, *hm = a.Hm + (int64_t)p * M;
-    const bool on = p < min(*a.n_nodes, a.cap) && a.ver[p] >= 0;
-    if (!on) {
-        for (int k = lane; k < D_x; k += kWave)
-            x[k] = 0.f;
-        for (int k = lane; k < M; k += kWave)
-            hm[k] = 0.f;
-        return;
-    }
-    const float *ml = a.mail + (int64_t)p * D_m;
-    for (int k = lane; k < D_m; k += kWave)
-        x[k] = ml[k];
-    const double dt = a.mail_ts[p] - a.mem_ts[p];
-    for (int d = lane; d < D_t; d += kWave)
-        x[D_m + d] = time_enc(a.omega[d], a.beta[d], dt);
-    for (int k = lane; k < M; k += kWave)
-        hm[k] = a.mem[(int64_t)p * M + k];
-}
-
 // One thread per (node, hidden unit): the gates again from Gx = X W_ih^t +
 // b_ih and Gh = Hm W_hh^t + b_hh, then the gradients of the gate
 // pre-activations: dGx = [da_r | da_z | da_n], dGh = [da_r | da_z | da_n r].
@@ -680,8 +637,10 @@ __global__ __launch_bounds__(256) void k_gru_bwd(const int32_t *__restrict__ n_n
     if (t >= (int64_t)cap * M)
         return;
     const int p = (int)(t / M), j = (int)(t % M);
+    if (p >= min(*n_nodes, cap))   // the weight gradients' sums end at the node set
+        return;
     const int64_t o = (int64_t)p * 3 * M;
-    if (p >= min(*n_nodes, cap) || ver[p] < 0) {
+    if (ver[p] < 0) {
         dGx[o + j] = dGx[o + M + j] = dGx[o + 2 * M + j] = 0.f;
         dGh[o + j] = dGh[o + M + j] = dGh[o + 2 * M + j] = 0.f;
         return;
@@ -703,36 +662,102 @@ __global__ __launch_bounds__(256) void k_gru_bwd(const int32_t *__restrict__ n_n
 }
 
 // ------------------------------------------------------------- optimizer
-__global__ __launch_bounds__(256) void k_sgd(float *__restrict__ theta, const float *__restrict__ g,
-                                             int64_t n, float lr)
-{
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t < n)
-        theta[t] -= lr * g[t];
-}
+// The end of a step, one thread per parameter: its gradient from the split
+// products (added in split order), then the optimizer.  Tensor k's element
+// (row, col) is sum_z part[z stride + row ld + col]; columns at or past ld
+// (the query's time columns, whose input is phi(0) for every root) are the
+// row's sum times phi(0).  b_k has no part: its gradient is zero, since it
+// shifts all the scores of a head alike.  One more workgroup sums the loss
+// and b_out's gradient in a fixed order, the latter pair by pair: the positive
+// and the negative scores' gradients nearly cancel.
+struct GradSeg {
+    int64_t off;           // first parameter
+    int cols, ld, splits;
+    const float *part;     // null: zero
+    int64_t stride;
+    const float *rows;     // row sums [splits][rows_stride] for the columns past ld
+    int64_t rows_stride;
+};
 
-// Adam with bias correction: c1 = 1 - beta1^t, c2 = 1 - beta2^t
-__global__ __launch_bounds__(256) void k_adam(float *__restrict__ theta,
-                                              const float *__restrict__ g, float *__restrict__ m1,
-                                              float *__restrict__ m2, int64_t n, float lr,
-                                              float b1, float b2, float eps, float c1, float c2)
+struct FinishArgs {
+    GradSeg seg[17];
+    int64_t n;
+    float *theta, *grad, *m1, *m2;
+    const double *omega, *beta;
+    int adam;
+    float lr, b1, b2, eps, c1, c2;   // c1 = 1 - b1^t, c2 = 1 - b2^t
+    const float *lossv, *dsc;
+    int b;
+    float *loss, *loss_out;
+};
+
+__device__ __forceinline__ void optimize(const FinishArgs &f, int64_t t, float g)
 {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= n)
+    f.grad[t] = g;
+    if (!f.adam) {
+        f.theta[t] -= f.lr * g;
         return;
-    const float gt = g[t];
-    const float a = b1 * m1[t] + (1.f - b1) * gt;
-    const float v = b2 * m2[t] + (1.f - b2) * gt * gt;
-    m1[t] = a;
-    m2[t] = v;
-    theta[t] -= lr * (a / c1) / (sqrtf(v / c2) + eps);
+    }
+    const float a = f.b1 * f.m1[t] + (1.f - f.b1) * g;
+    const float v = f.b2 * f.m2[t] + (1.f - f.b2) * g * g;
+    f.m1[t] = a;
+    f.m2[t] = v;
+    f.theta[t] -= f.lr * (a / f.c1) / (sqrtf(v / f.c2) + f.eps);
 }
 
-__global__ __launch_bounds__(256) void k_fill_f32(float *__restrict__ p, int64_t n, float v)
+__global__ __launch_bounds__(256) void k_grad_finish(FinishArgs f)
 {
+    if (blockIdx.x == gridDim.x - 1) {   // loss = (1/b) sum of the events' losses; b_out
+        __shared__ float sum[2][256];
+        float x = 0.f, y = 0.f;
+        for (int e = threadIdx.x; e < f.b; e += 256) {
+            x += f.lossv[e];
+            y += f.dsc[e] + f.dsc[f.b + e];
+        }
+        sum[0][threadIdx.x] = x;
+        sum[1][threadIdx.x] = y;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) {
+                sum[0][threadIdx.x] += sum[0][threadIdx.x + w];
+                sum[1][threadIdx.x] += sum[1][threadIdx.x + w];
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            const float l = sum[0][0] / (float)f.b;
+            *f.loss = l;
+            if (f.loss_out)
+                *f.loss_out = l;
+            optimize(f, f.n - 1, sum[1][0]);
+        }
+        return;
+    }
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t < n)
-        p[t] = v;
+    if (t >= f.n - 1)
+        return;
+    int k = 0;
+    while (k < 16 && t >= f.seg[k + 1].off)
+        ++k;
+    const GradSeg &s = f.seg[k];
+    const int i = (int)(t - s.off), row = i / s.cols, col = i - row * s.cols;
+    float g = 0.f;
+    if (s.part) {
+        const bool past = col >= s.ld;
+        const float *p = past ? s.rows + row : s.part + (int64_t)row * s.ld + col;
+        const int64_t stride = past ? s.rows_stride : s.stride;
+        int z = 0;
+        for (; z + 4 <= s.splits; z += 4) {
+            const float x0 = p[z * stride], x1 = p[(z + 1) * stride], x2 = p[(z + 2) * stride],
+                        x3 = p[(z + 3) * stride];
+            g = (((g + x0) + x1) + x2) + x3;
+        }
+        for (; z < s.splits; ++z)
+            g += p[z * stride];
+        if (past)
+            g *= time_enc(f.omega[col - s.ld], f.beta[col - s.ld], 0.0);
+    }
+    optimize(f, t, g);
 }
 
 constexpr int kNParams = 17;
@@ -749,19 +774,20 @@ struct tgm_trainer {
     int64_t n_params = 0;
     int64_t off[kNParams + 1] = {};
     float *theta = nullptr, *grad = nullptr, *m1 = nullptr, *m2 = nullptr;
+    int32_t ldu = 0, ldx = 0;   // row strides of the (root, head) rows and of X
     // work space
-    float *ones = nullptr, *part = nullptr;
-    int64_t part_floats = 0;
+    float *part = nullptr;      // split weight gradients, see train_grads
     float *Zs = nullptr, *Zd = nullptr, *dZsrc = nullptr, *dZdst = nullptr, *act = nullptr;
-    float *dsc = nullptr, *lossv = nullptr, *loss = nullptr;
-    float *dh = nullptr, *Xq = nullptr, *Q = nullptr, *kap = nullptr, *KV = nullptr;
-    float *alpha = nullptr, *Xo = nullptr, *O = nullptr, *dO = nullptr, *dXo = nullptr;
-    float *dKV = nullptr, *dQ = nullptr, *dKm = nullptr, *dXq = nullptr, *ds = nullptr;
+    float *dsc = nullptr, *lossv = nullptr, *loss = nullptr, *cq = nullptr;
+    float *Q = nullptr, *Xo = nullptr, *dO = nullptr, *dXo = nullptr,
+          *dQ = nullptr;
+    float *U = nullptr, *abar = nullptr, *dbar = nullptr;   // [R x H x ldu]; dbar: dabar, then du
+    float *alpha = nullptr, *dKm = nullptr, *ds = nullptr;
     float *X = nullptr, *Hm = nullptr, *Gx = nullptr, *Gh = nullptr, *dGx = nullptr,
           *dGh = nullptr;
-    uint64_t *keys = nullptr, *keys_sorted = nullptr;
-    int32_t *seg = nullptr, *seg_end = nullptr, *chunk_off = nullptr;
-    float *ds_part = nullptr;   // [(R + S) / kDsChunk + max_nodes] x M chunk sums
+    uint32_t *keys = nullptr, *keys_sorted = nullptr;   // node-set positions
+    int32_t *vals = nullptr, *vals_sorted = nullptr;    // contributors
+    float *ds_head = nullptr, *ds_tail = nullptr;       // [sorted blocks x M] open runs
     void *sort_tmp = nullptr;
     size_t sort_bytes = 0;
     float *p(int k) const { return theta + off[k]; }
@@ -770,96 +796,88 @@ struct tgm_trainer {
 
 namespace {
 
-// C = op(A) op(B) (+ bias) (+ C): split-K when the output has few tiles and
-// the reduction is long (the weight gradients), so the grid fills the GPU
-tgm_status_t gemm(const tgm_trainer *tr, bool ta, bool tb, int m, int n, int k, const float *A,
-                  int lda, const float *B, int ldb, float *C, int ldc, const float *bias,
-                  bool accumulate, hipStream_t s)
+// Parts a weight gradient's reduction is cut into at most, and at least the
+// length of a part.
+constexpr int kMaxSplits = 32, kMinSplit = 256, kGradBlocks = 2048;
+
+// Bits that hold the sort keys 0 .. nodes
+int key_bits(int32_t nodes)
 {
-    if (m <= 0 || n <= 0)
-        return TGM_OK;
-    GemmArgs g;
-    g.m = m;
-    g.n = n;
-    g.k = k;
-    g.A = A;
-    g.lda = lda;
-    g.B = B;
-    g.ldb = ldb;
-    g.C = C;
-    g.ldc = ldc;
-    g.bias = bias;
-    g.accumulate = accumulate ? 1 : 0;
-    g.part = tr->part;
-    g.m_live = nullptr;
-    const int64_t tiles = cdiv(m, kGT) * cdiv(n, kGT);
-    int splits = 1;
-    if (tiles < 512 && k > 4 * kGK * 16) {
-        splits = (int)std::min<int64_t>(cdiv(k, 256), std::max<int64_t>(1, 1024 / tiles));
-        splits = std::min(splits, kMaxSplits);
-        while (splits > 1 && (int64_t)splits * m * n > tr->part_floats)
-            --splits;
-    }
-    int kchunk = round_up((int32_t)cdiv(std::max(k, 1), splits), kGK);
-    splits = std::max(1, (int)cdiv(std::max(k, 1), kchunk));
-    g.splits = splits;
-    g.kchunk = kchunk;
-    const dim3 grid((unsigned)cdiv(n, kGT), (unsigned)cdiv(m, kGT), (unsigned)splits);
-    if (!ta && !tb)
-        TGM_LAUNCH((k_gemm<false, false>), grid, dim3(256), 0, s, g);
-    else if (!ta && tb)
-        TGM_LAUNCH((k_gemm<false, true>), grid, dim3(256), 0, s, g);
-    else if (ta && !tb)
-        TGM_LAUNCH((k_gemm<true, false>), grid, dim3(256), 0, s, g);
+    int bits = 1;
+    while (bits < 31 && (int64_t(1) << bits) <= nodes)
+        ++bits;
+    return bits;
+}
+
+// out = x op(w): the products of the forward pass and of the gradients that
+// go back through it.  x [m x k] (leading dimension ldx).
+GemmProb mul(int m, int n, int k, const float *x, int ldx, const float *w, int ldw, float *out,
+             int ldo, const float *bias = nullptr)
+{
+    GemmProb p;
+    p.m = m;
+    p.n = n;
+    p.k = k;
+    p.A = x;
+    p.lda = ldx;
+    p.B = w;
+    p.ldb = ldw;
+    p.C = out;
+    p.ldc = ldo;
+    p.bias = bias;
+    return p;
+}
+
+// The same once per head, with the strides of one head in x, w and out
+GemmProb heads(GemmProb p, int H, int64_t sx, int64_t sw, int64_t so, int64_t sbias = 0)
+{
+    p.batch = H;
+    p.sA = sx;
+    p.sB = sw;
+    p.sC = so;
+    p.sBias = sbias;
+    return p;
+}
+
+// A weight gradient dw [m x n] = g^t x over at most `rows` rows, about
+// `expect` of them, cut into parts of about `len` rows at *at (advanced),
+// with g's row sums behind them.
+GemmProb grad_of(int m, int n, int rows, int expect, int len, const float *g, int ldg,
+                 const float *x, int ldx, float **at, int heads_ = 1)
+{
+    GemmProb p = mul(m, n, rows, g, ldg, x, ldx, *at, n);
+    p.splits = std::max(1, std::min(kMaxSplits, expect / len));
+    p.batch = heads_;
+    p.split_stride = (int64_t)heads_ * m * n;
+    p.sC = (int64_t)m * n;
+    p.colsum = *at + p.splits * p.split_stride;
+    p.colsum_stride = (int64_t)heads_ * m;
+    p.sColsum = m;
+    *at = p.colsum + p.splits * p.colsum_stride;
+    return p;
+}
+
+template <int CE, int CT, int NC>
+tgm_status_t att_launch(bool bwd, const AttArgs &a, hipStream_t s)
+{
+    const dim3 grid((unsigned)cdiv((int64_t)a.R * kWave, 256));
+    if (bwd)
+        TGM_LAUNCH((k_att_bwd<CE, CT, NC>), grid, dim3(256), 0, s, a);
     else
-        TGM_LAUNCH((k_gemm<true, true>), grid, dim3(256), 0, s, g);
-    if (splits > 1)
-        TGM_LAUNCH(k_gemm_reduce, dim3((unsigned)cdiv((int64_t)m * n, 256)), dim3(256), 0, s, g);
+        TGM_LAUNCH((k_att_fwd<CE, CT, NC>), grid, dim3(256), 0, s, a);
     return TGM_OK;
 }
 
-// column sums of X [rows x n] (leading dimension ldx): the bias gradients
-tgm_status_t colsum(const tgm_trainer *tr, int rows, int n, const float *X, int ldx, float *out,
-                    hipStream_t s)
+// Rows of up to 192 edge features and 128 time codes keep 10 slots (70
+// registers); wider ones take the larger row, 5 slots at a time.
+tgm_status_t att_dispatch(bool bwd, const AttArgs &a, hipStream_t s)
 {
-    return gemm(tr, true, false, 1, n, rows, tr->ones, 1, X, ldx, out, n, nullptr, false, s);
+    if (a.D_e <= 3 * kWave && a.D_t <= 2 * kWave)
+        return att_launch<3, 2, 10>(bwd, a, s);
+    return att_launch<4, 6, 5>(bwd, a, s);
 }
 
 }  // namespace
-
-tgm_status_t tgm::gemm_f32(bool ta, bool tb, int m, int n, int k, const float *A, int lda,
-                          const float *B, int ldb, float *C, int ldc, const float *bias,
-                          bool accumulate, hipStream_t s, const int32_t *m_live)
-{
-    if (m <= 0 || n <= 0)
-        return TGM_OK;
-    GemmArgs g;
-    g.m = m;
-    g.n = n;
-    g.k = k;
-    g.A = A;
-    g.lda = lda;
-    g.B = B;
-    g.ldb = ldb;
-    g.C = C;
-    g.ldc = ldc;
-    g.bias = bias;
-    g.accumulate = accumulate ? 1 : 0;
-    g.part = nullptr;
-    g.m_live = m_live;
-    g.splits = 1;
-    g.kchunk = round_up((int32_t)std::max(k, 1), kGK);
-    const dim3 grid((unsigned)cdiv(n, kGT), (unsigned)cdiv(m, kGT), 1);
-    if (!ta && !tb)
-        TGM_LAUNCH((k_gemm<false, false>), grid, dim3(256), 0, s, g);
-    else if (!ta && tb)
-        TGM_LAUNCH((k_gemm<false, true>), grid, dim3(256), 0, s, g);
-    else if (ta && !tb)
-        TGM_LAUNCH((k_gemm<true, false>), grid, dim3(256), 0, s, g);
-    else
-        TGM_LAUNCH((k_gemm<true, true>), grid, dim3(256), 0, s, g);
-    return TGM_OK;
-}
 
 // ======================================================================== API
 
@@ -867,20 +885,14 @@ extern "C" tgm_status_t tgm_trainer_destroy(tgm_trainer_t tr)
 {
     if (!tr)
         return TGM_EINVAL;
-    float *bufs[] = {tr->theta, tr->grad, tr->m1, tr->m2, tr->ones, tr->part, tr->Zs, tr->Zd,
-                     tr->dZsrc, tr->dZdst, tr->act, tr->dsc, tr->lossv, tr->loss, tr->dh, tr->Xq,
-                     tr->Q, tr->kap, tr->KV, tr->alpha, tr->Xo, tr->O, tr->dO, tr->dXo, tr->dKV,
-                     tr->dQ, tr->dKm, tr->dXq, tr->ds, tr->X, tr->Hm, tr->Gx, tr->Gh, tr->dGx,
-                     tr->dGh};
-    for (float *b : bufs)
+    void *bufs[] = {tr->theta, tr->grad, tr->m1, tr->m2, tr->part, tr->Zs, tr->Zd, tr->dZsrc,
+                    tr->dZdst, tr->act, tr->dsc, tr->lossv, tr->loss, tr->cq, tr->Q,
+                    tr->Xo, tr->dO, tr->dXo, tr->dQ, tr->U, tr->abar, tr->dbar, tr->alpha,
+                    tr->dKm, tr->ds, tr->X, tr->Hm, tr->Gx, tr->Gh, tr->dGx, tr->dGh, tr->keys,
+                    tr->keys_sorted, tr->vals, tr->vals_sorted, tr->ds_head, tr->ds_tail,
+                    tr->sort_tmp};
+    for (void *b : bufs)
         (void)hipFree(b);
-    (void)hipFree(tr->keys);
-    (void)hipFree(tr->keys_sorted);
-    (void)hipFree(tr->seg);
-    (void)hipFree(tr->seg_end);
-    (void)hipFree(tr->chunk_off);
-    (void)hipFree(tr->ds_part);
-    (void)hipFree(tr->sort_tmp);
     delete tr;
     return TGM_OK;
 }
@@ -933,11 +945,13 @@ extern "C" tgm_status_t tgm_trainer_create(tgm_model_t m, const tgm_weights *w,
         tr->off[k + 1] = tr->off[k] + sizes[k];
     tr->n_params = tr->off[kNParams];
     const int64_t R = tr->max_roots, B = tr->max_b, S = R * nb, C = tr->max_nodes;
-    const int64_t n_items = R + S;
-    // the largest weight-gradient output times the largest split count
-    const int64_t mn = std::max<int64_t>({3 * M * D_x, 2 * (int64_t)M * Dkv, M * Dq,
-                                          2 * (int64_t)M * M, 3 * (int64_t)M * M});
-    tr->part_floats = (int64_t)kMaxSplits * mn;
+    const int64_t n_items = R + S, H = tr->H, blocks = cdiv(n_items, kWave);
+    tr->ldu = round_up((int32_t)Dkv, 4);
+    tr->ldx = round_up((int32_t)D_x, 4);
+    int64_t part = 0;   // every split product and its row sums at kMaxSplits
+    for (const auto &mn : {std::pair<int64_t, int64_t>{3 * M, D_x}, {3 * M, M}, {M, M}, {M, Dkv},
+                           {M, Dkv}, {M, 2 * M}, {M, M}, {M, M}, {1, M}})
+        part += kMaxSplits * mn.first * (mn.second + 1);
     tgm_status_t st = TGM_OK;
     auto alloc = [&](auto **ptr, int64_t count) {
         if (st == TGM_OK &&
@@ -948,8 +962,7 @@ extern "C" tgm_status_t tgm_trainer_create(tgm_model_t m, const tgm_weights *w,
     alloc(&tr->grad, tr->n_params);
     alloc(&tr->m1, tr->n_params);
     alloc(&tr->m2, tr->n_params);
-    alloc(&tr->ones, std::max({S, C, R}));
-    alloc(&tr->part, tr->part_floats);
+    alloc(&tr->part, part);
     alloc(&tr->Zs, B * M);
     alloc(&tr->Zd, 2 * B * M);
     alloc(&tr->dZsrc, B * M);
@@ -958,22 +971,19 @@ extern "C" tgm_status_t tgm_trainer_create(tgm_model_t m, const tgm_weights *w,
     alloc(&tr->dsc, 2 * B);
     alloc(&tr->lossv, B);
     alloc(&tr->loss, 1);
-    alloc(&tr->dh, R * M);
-    alloc(&tr->Xq, R * Dq);
+    alloc(&tr->cq, M);
     alloc(&tr->Q, R * M);
-    alloc(&tr->kap, S * Dkv);
-    alloc(&tr->KV, S * 2 * M);
-    alloc(&tr->alpha, R * tr->H * nb);
     alloc(&tr->Xo, R * 2 * M);
-    alloc(&tr->O, R * M);
     alloc(&tr->dO, R * M);
     alloc(&tr->dXo, R * 2 * M);
-    alloc(&tr->dKV, S * 2 * M);
     alloc(&tr->dQ, R * M);
+    alloc(&tr->U, R * H * tr->ldu);
+    alloc(&tr->abar, R * H * tr->ldu);
+    alloc(&tr->dbar, R * H * tr->ldu);
+    alloc(&tr->alpha, R * H * nb);
     alloc(&tr->dKm, S * M);
-    alloc(&tr->dXq, R * M);
     alloc(&tr->ds, C * M);
-    alloc(&tr->X, C * D_x);
+    alloc(&tr->X, C * tr->ldx);
     alloc(&tr->Hm, C * M);
     alloc(&tr->Gx, C * 3 * M);
     alloc(&tr->Gh, C * 3 * M);
@@ -981,17 +991,21 @@ extern "C" tgm_status_t tgm_trainer_create(tgm_model_t m, const tgm_weights *w,
     alloc(&tr->dGh, C * 3 * M);
     alloc(&tr->keys, n_items);
     alloc(&tr->keys_sorted, n_items);
-    alloc(&tr->seg, C);
-    alloc(&tr->seg_end, C);
-    alloc(&tr->chunk_off, C + 1);
-    alloc(&tr->ds_part, (n_items / kDsChunk + C + 1) * M);
+    alloc(&tr->vals, n_items);
+    alloc(&tr->vals_sorted, n_items);
+    alloc(&tr->ds_head, blocks * M);
+    alloc(&tr->ds_tail, blocks * M);
     if (st == TGM_OK) {
-        size_t bytes = 0;
-        if (hipcub::DeviceRadixSort::SortKeys(nullptr, bytes, tr->keys, tr->keys_sorted,
-                                              (int)n_items, 0, 64) != hipSuccess)
-            st = TGM_EDEVICE;
-        tr->sort_bytes = bytes;
-        alloc((char **)&tr->sort_tmp, (int64_t)bytes);
+        // the sort picks its method by size: room for every size it may get
+        for (int64_t n = n_items; n > 0 && st == TGM_OK; n /= 2) {
+            size_t bytes = 0;
+            if (hipcub::DeviceRadixSort::SortPairs(nullptr, bytes, tr->keys, tr->keys_sorted,
+                                                   tr->vals, tr->vals_sorted, (int)n, 0,
+                                                   key_bits(tr->max_nodes)) != hipSuccess)
+                st = TGM_EDEVICE;
+            tr->sort_bytes = std::max(tr->sort_bytes, bytes);
+        }
+        alloc((char **)&tr->sort_tmp, (int64_t)tr->sort_bytes);
     }
     if (st != TGM_OK) {
         tgm_trainer_destroy(tr);
@@ -1012,16 +1026,8 @@ extern "C" tgm_status_t tgm_trainer_create(tgm_model_t m, const tgm_weights *w,
          hipMemsetAsync(tr->m2, 0, sizeof(float) * tr->n_params, s) != hipSuccess ||
          hipMemsetAsync(tr->grad, 0, sizeof(float) * tr->n_params, s) != hipSuccess ||
          hipMemsetAsync(tr->loss, 0, sizeof(float), s) != hipSuccess ||
-         hipMemsetAsync(tr->seg, 0, sizeof(int32_t) * C, s) != hipSuccess ||
-         hipMemsetAsync(tr->seg_end, 0, sizeof(int32_t) * C, s) != hipSuccess))
+         hipStreamSynchronize(s) != hipSuccess))
         st = TGM_EDEVICE;
-    if (st == TGM_OK) {
-        const int64_t n1 = std::max({S, C, R});
-        hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)cdiv(n1, 256)), dim3(256), 0, s, tr->ones,
-                           n1, 1.f);
-        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
-            st = TGM_EDEVICE;
-    }
     if (st != TGM_OK) {
         tgm_trainer_destroy(tr);
         return st;
@@ -1077,124 +1083,158 @@ tgm_status_t tgm::train_step_launch(tgm_trainer_t tr, tgm_model_t m, tgm_graph_t
         return TGM_EINVAL;
     if (g->D_e != tr->D_e || (tr->D_e > 0 && !g->efeat))
         return TGM_EINVAL;
-    const int M = tr->M, nb = tr->nb, R = 3 * b, Dq = tr->Dq, Dkv = tr->Dkv, D_x = tr->D_x;
-    const int64_t S = (int64_t)R * nb;
+    const int M = tr->M, nb = tr->nb, R = 3 * b, H = tr->H, dh = M / H;
+    const int Dq = tr->Dq, Dkv = tr->Dkv, D_x = tr->D_x, ldu = tr->ldu, ldx = tr->ldx;
+    const int64_t S = (int64_t)R * nb, n_items = R + S;
     const float *W_ih = tr->p(0), *W_hh = tr->p(1), *b_ih = tr->p(2), *b_hh = tr->p(3);
     const float *W_q = tr->p(4), *b_q = tr->p(5), *W_k = tr->p(6), *b_k = tr->p(7);
     const float *W_v = tr->p(8), *b_v = tr->p(9), *W_o = tr->p(10), *b_o = tr->p(11);
     const float *W_src = tr->p(12), *W_dst = tr->p(13);
+    const float *h_rest = h + (int64_t)b * M;
+    float *s_v = tr->Xo + M;   // the roots' new memories, rows of 2M
 
-    // link predictor and loss
-    TGM_TRY_STATUS(gemm(tr, false, true, b, M, M, h, M, W_src, M, tr->Zs, M, nullptr, false, s));
-    TGM_TRY_STATUS(gemm(tr, false, true, 2 * b, M, M, h + (int64_t)b * M, M, W_dst, M, tr->Zd, M,
-                        nullptr, false, s));
+    RowArgs ra{R, nb, M, tr->D_m, tr->D_t, cap, ldx, (int)cdiv(R, 4), (int)cdiv(cap, 4),
+               (int)cdiv(n_items, 256), sb.root_pos, sb.nbr_pos, sb.cnt, sb.n_nodes, fb.ver,
+               fb.mem_ts, fb.mail_ts, m->omega, m->beta, mem_new, fb.mem, fb.mail, W_q, b_q,
+               tr->Xo, tr->X, tr->Hm, tr->cq, tr->keys, tr->vals};
+    TGM_LAUNCH(k_train_rows,
+               dim3((unsigned)(ra.n_root + ra.n_node + ra.n_key + cdiv(M, 4))), dim3(256), 0, s,
+               ra);
+    // the predictor's layers, the queries and the GRU's gates
+    {
+        GemmProb g[5] = {mul(b, M, M, h, M, W_src, M, tr->Zs, M),
+                         mul(2 * b, M, M, h_rest, M, W_dst, M, tr->Zd, M),
+                         mul(R, M, M, s_v, 2 * M, W_q, Dq, tr->Q, M, tr->cq),
+                         mul(cap, 3 * M, D_x, tr->X, ldx, W_ih, D_x, tr->Gx, 3 * M, b_ih),
+                         mul(cap, 3 * M, M, tr->Hm, M, W_hh, M, tr->Gh, 3 * M, b_hh)};
+        g[3].live = g[4].live = sb.n_nodes;
+        TGM_TRY_STATUS(gemm_launch(false, true, g, 5, s));
+    }
     PredArgs pa{b, M, tr->Zs, tr->Zd, tr->p(14), tr->p(15), tr->p(16), tr->dZsrc, tr->dZdst,
                 tr->act, tr->dsc, tr->lossv};
     TGM_LAUNCH(k_pred, dim3((unsigned)cdiv((int64_t)b * kWave, 256)), dim3(256), 0, s, pa);
-    TGM_LAUNCH(k_loss, dim3(1), dim3(256), 0, s, tr->lossv, b, tr->loss);
-    if (loss_out)
-        TGM_HIP(hipMemcpyAsync(loss_out, tr->loss, sizeof(float), hipMemcpyDeviceToDevice, s));
-    // predictor gradients; the gradient of h
-    TGM_TRY_STATUS(gemm(tr, true, false, 1, M, 2 * b, tr->dsc, 1, tr->act, M, tr->gr(15), M,
-                        nullptr, false, s));
-    TGM_TRY_STATUS(gemm(tr, true, false, 1, 1, 2 * b, tr->ones, 1, tr->dsc, 1, tr->gr(16), 1,
-                        nullptr, false, s));
-    TGM_TRY_STATUS(colsum(tr, b, M, tr->dZsrc, M, tr->gr(14), s));
-    TGM_TRY_STATUS(gemm(tr, true, false, M, M, b, tr->dZsrc, M, h, M, tr->gr(12), M, nullptr,
-                        false, s));
-    TGM_TRY_STATUS(gemm(tr, true, false, M, M, 2 * b, tr->dZdst, M, h + (int64_t)b * M, M,
-                        tr->gr(13), M, nullptr, false, s));
-    TGM_TRY_STATUS(gemm(tr, false, false, b, M, M, tr->dZsrc, M, W_src, M, tr->dh, M, nullptr,
-                        false, s));
-    TGM_TRY_STATUS(gemm(tr, false, false, 2 * b, M, M, tr->dZdst, M, W_dst, M,
-                        tr->dh + (int64_t)b * M, M, nullptr, false, s));
-
-    // attention: its inputs and intermediate values again
-    RowArgs ra{R, nb, M, tr->D_e, tr->D_t, sb.root_pos, sb.nbr_pos, sb.eid, sb.cnt, sb.root_ts,
-               sb.nts, m->omega, m->beta, mem_new, g->efeat, tr->Xq, tr->kap};
-    TGM_LAUNCH(k_att_rows, dim3((unsigned)cdiv((R + S) * kWave, 256)), dim3(256), 0, s, ra);
-    TGM_TRY_STATUS(gemm(tr, false, true, R, M, Dq, tr->Xq, Dq, W_q, Dq, tr->Q, M, b_q, false, s));
-    TGM_TRY_STATUS(gemm(tr, false, true, (int)S, M, Dkv, tr->kap, Dkv, W_k, Dkv, tr->KV, 2 * M,
-                        b_k, false, s));
-    TGM_TRY_STATUS(gemm(tr, false, true, (int)S, M, Dkv, tr->kap, Dkv, W_v, Dkv, tr->KV + M,
-                        2 * M, b_v, false, s));
-    CoreArgs ca{R, nb, M, tr->H, 1.f / sqrtf((float)(M / tr->H)), sb.cnt, sb.root_pos, tr->Q,
-                tr->KV, mem_new, tr->dXo, tr->alpha, tr->Xo, tr->dKV, tr->dQ};
-    TGM_LAUNCH(k_att_core, dim3((unsigned)cdiv((int64_t)R * kWave, 256)), dim3(256), 0, s, ca);
-    TGM_TRY_STATUS(gemm(tr, false, true, R, M, 2 * M, tr->Xo, 2 * M, W_o, 2 * M, tr->O, M, b_o,
-                        false, s));
-    // attention backward
-    TGM_LAUNCH(k_relu_mask, dim3((unsigned)cdiv((int64_t)R * M, 256)), dim3(256), 0, s, tr->dh,
-               tr->O, tr->dO, (int64_t)R * M);
-    TGM_TRY_STATUS(gemm(tr, true, false, M, 2 * M, R, tr->dO, M, tr->Xo, 2 * M, tr->gr(10), 2 * M,
-                        nullptr, false, s));
-    TGM_TRY_STATUS(colsum(tr, R, M, tr->dO, M, tr->gr(11), s));
-    TGM_TRY_STATUS(gemm(tr, false, false, R, 2 * M, M, tr->dO, M, W_o, 2 * M, tr->dXo, 2 * M,
-                        nullptr, false, s));
-    TGM_LAUNCH(k_att_core_bwd, dim3((unsigned)cdiv((int64_t)R * kWave, 256)), dim3(256), 0, s,
-               ca);
-    TGM_TRY_STATUS(gemm(tr, true, false, M, Dkv, (int)S, tr->dKV, 2 * M, tr->kap, Dkv, tr->gr(6),
-                        Dkv, nullptr, false, s));
-    TGM_TRY_STATUS(gemm(tr, true, false, M, Dkv, (int)S, tr->dKV + M, 2 * M, tr->kap, Dkv,
-                        tr->gr(8), Dkv, nullptr, false, s));
-    TGM_TRY_STATUS(colsum(tr, (int)S, M, tr->dKV, 2 * M, tr->gr(7), s));
-    TGM_TRY_STATUS(colsum(tr, (int)S, M, tr->dKV + M, 2 * M, tr->gr(9), s));
-    TGM_TRY_STATUS(gemm(tr, true, false, M, Dq, R, tr->dQ, M, tr->Xq, Dq, tr->gr(4), Dq, nullptr,
-                        false, s));
-    TGM_TRY_STATUS(colsum(tr, R, M, tr->dQ, M, tr->gr(5), s));
-    // gradients of the updated memories the attention read: slots, roots
-    TGM_TRY_STATUS(gemm(tr, false, false, (int)S, M, M, tr->dKV, 2 * M, W_k, Dkv, tr->dKm, M,
-                        nullptr, false, s));
-    TGM_TRY_STATUS(gemm(tr, false, false, (int)S, M, M, tr->dKV + M, 2 * M, W_v, Dkv, tr->dKm, M,
-                        nullptr, true, s));
-    TGM_TRY_STATUS(gemm(tr, false, false, R, M, M, tr->dQ, M, W_q, Dq, tr->dXq, M, nullptr,
-                        false, s));
-    const int64_t n_items = R + S;
-    TGM_LAUNCH(k_ds_keys, dim3((unsigned)cdiv(n_items, 256)), dim3(256), 0, s, R, nb,
-               sb.root_pos, sb.nbr_pos, sb.cnt, tr->keys);
+    // u = W_k^t q per head; the gradient of the output projection, h's where
+    // its ReLU let the value through
+    {
+        GemmProb g[3] = {
+            heads(mul(R, Dkv, dh, tr->Q, M, W_k, Dkv, tr->U, H * ldu), H, dh, (int64_t)dh * Dkv,
+                  ldu),
+            mul(b, M, M, tr->dZsrc, M, W_src, M, tr->dO, M),
+            mul(2 * b, M, M, tr->dZdst, M, W_dst, M, tr->dO + (int64_t)b * M, M)};
+        g[1].gate = h;
+        g[2].gate = h_rest;
+        g[1].ldg = g[2].ldg = M;
+        TGM_TRY_STATUS(gemm_launch(false, false, g, 3, s));
+    }
+    AttArgs aa{R, nb, M, tr->D_e, tr->D_t, H, ldu, 1.f / sqrtf((float)dh), sb.cnt, sb.root_pos,
+               sb.nbr_pos, sb.eid, sb.root_ts, sb.nts, m->omega, m->beta, mem_new, g->efeat,
+               tr->U, tr->alpha, tr->abar, tr->dbar, tr->dKm};
+    TGM_TRY_STATUS(att_dispatch(false, aa, s));
+    {   // o = W_v abar + b_v per head (zero without neighbours)
+        GemmProb p = heads(mul(R, dh, Dkv, tr->abar, H * ldu, W_v, Dkv, tr->Xo, 2 * M, b_v), H,
+                           ldu, (int64_t)dh * Dkv, dh, dh);
+        p.row_on = sb.cnt;
+        p.zero_cols = dh;
+        TGM_TRY_STATUS(gemm_launch(false, true, &p, 1, s));
+    }
+    {   // gradient of [o || s'_v]; o is no output of a root without neighbours
+        GemmProb p = mul(R, 2 * M, M, tr->dO, M, W_o, 2 * M, tr->dXo, 2 * M);
+        p.row_on = sb.cnt;
+        p.zero_cols = M;
+        TGM_TRY_STATUS(gemm_launch(false, false, &p, 1, s));
+    }
+    {   // dabar = W_v^t do per head
+        const GemmProb p = heads(mul(R, Dkv, dh, tr->dXo, 2 * M, W_v, Dkv, tr->dbar, H * ldu), H,
+                                 dh, (int64_t)dh * Dkv, ldu);
+        TGM_TRY_STATUS(gemm_launch(false, false, &p, 1, s));
+    }
+    TGM_TRY_STATUS(att_dispatch(true, aa, s));
+    {   // dq = W_k du per head, then its part of the roots' gradient of s'_v
+        GemmProb p = heads(mul(R, dh, Dkv, tr->dbar, H * ldu, W_k, Dkv, tr->dQ, M), H, ldu,
+                           (int64_t)dh * Dkv, dh);
+        TGM_TRY_STATUS(gemm_launch(false, true, &p, 1, s));
+        GemmProb v = mul(R, M, M, tr->dQ, M, W_q, Dq, tr->dXo + M, 2 * M);
+        v.accumulate = 1;
+        TGM_TRY_STATUS(gemm_launch(false, false, &v, 1, s));
+    }
+    // each node's gradient: its contributors' rows, sorted by node
     size_t sort_bytes = tr->sort_bytes;
-    TGM_HIP(hipcub::DeviceRadixSort::SortKeys(tr->sort_tmp, sort_bytes, tr->keys,
-                                              tr->keys_sorted, (int)n_items, 0, 64, s));
-    TGM_LAUNCH(k_ds_bounds, dim3((unsigned)cdiv(n_items, 256)), dim3(256), 0, s, n_items,
-               tr->keys_sorted, cap, tr->seg, tr->seg_end);
-    TGM_LAUNCH(k_ds_chunks, dim3(1), dim3(kDsScanThreads), 0, s, sb.n_nodes, cap, tr->seg,
-               tr->seg_end, tr->chunk_off);
-    TGM_LAUNCH(k_ds_partial, dim3(2048), dim3(256), 0, s, cap, M, R, n_items, tr->keys_sorted,
-               tr->seg, tr->seg_end, tr->chunk_off, tr->dXq, tr->dXo, tr->dKm, tr->ds_part);
-    TGM_LAUNCH(k_ds, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)), dim3(256), 0, s,
-               sb.n_nodes, cap, M, tr->chunk_off, tr->ds_part, tr->ds);
-
+    TGM_HIP(hipcub::DeviceRadixSort::SortPairs(tr->sort_tmp, sort_bytes, tr->keys,
+                                               tr->keys_sorted, tr->vals, tr->vals_sorted,
+                                               (int)n_items, 0, key_bits(cap), s));
+    TGM_LAUNCH(k_ds_block, dim3((unsigned)cdiv(n_items, 256)), dim3(256), 0, s, n_items, cap, M,
+               R, tr->keys_sorted, tr->vals_sorted, tr->dXo, tr->dKm, tr->ds, tr->ds_head,
+               tr->ds_tail);
+    TGM_LAUNCH(k_ds_join, dim3((unsigned)cdiv(n_items, 256)), dim3(256), 0, s, n_items, cap, M,
+               tr->keys_sorted, tr->ds_head, tr->ds_tail, tr->ds);
     // memory updater (GRU) backward
-    GruRowArgs gra{sb.n_nodes, cap, M, tr->D_m, tr->D_t, fb.mem, fb.mail, fb.mem_ts, fb.mail_ts,
-                   m->omega, m->beta, fb.ver, tr->X, tr->Hm};
-    TGM_LAUNCH(k_gru_rows, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)), dim3(256), 0, s,
-               gra);
-    TGM_TRY_STATUS(gemm(tr, false, true, cap, 3 * M, D_x, tr->X, D_x, W_ih, D_x, tr->Gx, 3 * M,
-                        b_ih, false, s));
-    TGM_TRY_STATUS(gemm(tr, false, true, cap, 3 * M, M, tr->Hm, M, W_hh, M, tr->Gh, 3 * M, b_hh,
-                        false, s));
     TGM_LAUNCH(k_gru_bwd, dim3((unsigned)cdiv((int64_t)cap * M, 256)), dim3(256), 0, s,
                sb.n_nodes, cap, M, fb.ver, tr->Gx, tr->Gh, tr->Hm, tr->ds, tr->dGx, tr->dGh);
-    TGM_TRY_STATUS(gemm(tr, true, false, 3 * M, D_x, cap, tr->dGx, 3 * M, tr->X, D_x, tr->gr(0),
-                        D_x, nullptr, false, s));
-    TGM_TRY_STATUS(gemm(tr, true, false, 3 * M, M, cap, tr->dGh, 3 * M, tr->Hm, M, tr->gr(1), M,
-                        nullptr, false, s));
-    TGM_TRY_STATUS(colsum(tr, cap, 3 * M, tr->dGx, 3 * M, tr->gr(2), s));
-    TGM_TRY_STATUS(colsum(tr, cap, 3 * M, tr->dGh, 3 * M, tr->gr(3), s));
-
-    // optimizer step, then the model's packed operands from the new weights
+    // every weight gradient, then the optimizer
+    // (a batch's node set has about as many nodes as roots: hubs recur)
+    const int nodes = std::min(cap, R + R / 2);
+    float *at = tr->part;
+    const int64_t tiles = cdiv(3 * M, 64) * (cdiv(D_x, 64) + cdiv(M, 112)) * nodes +
+                          (2 * H * cdiv(dh, 64) * cdiv(Dkv, 112) + 3 * cdiv(M, 64)) * R;
+    const int len = (int)std::max<int64_t>(kMinSplit, tiles / kGradBlocks);
+    GemmProb w[9] = {
+        grad_of(3 * M, D_x, cap, nodes, len, tr->dGx, 3 * M, tr->X, ldx, &at),
+        grad_of(3 * M, M, cap, nodes, len, tr->dGh, 3 * M, tr->Hm, M, &at),
+        grad_of(M, M, R, R, len, tr->dQ, M, s_v, 2 * M, &at),
+        grad_of(dh, Dkv, R, R, len, tr->Q, M, tr->dbar, H * ldu, &at, H),
+        grad_of(dh, Dkv, R, R, len, tr->dXo, 2 * M, tr->abar, H * ldu, &at, H),
+        grad_of(M, 2 * M, R, R, len, tr->dO, M, tr->Xo, 2 * M, &at),
+        grad_of(M, M, b, b, len, tr->dZsrc, M, h, M, &at),
+        grad_of(M, M, 2 * b, 2 * b, len, tr->dZdst, M, h_rest, M, &at),
+        grad_of(1, M, 2 * b, 2 * b, len, tr->dsc, 1, tr->act, M, &at)};
+    w[0].live = w[1].live = sb.n_nodes;
+    w[3].sA = w[4].sA = dh;
+    w[3].sB = w[4].sB = ldu;
+    TGM_TRY_STATUS(gemm_launch(true, false, w, 9, s));
     tr->steps++;
-    const int64_t n = tr->n_params;
-    if (tr->opt == TGM_OPT_SGD) {
-        TGM_LAUNCH(k_sgd, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, tr->theta, tr->grad, n,
-                   tr->lr);
-    } else {
-        const double c1 = 1.0 - std::pow((double)tr->beta1, (double)tr->steps);
-        const double c2 = 1.0 - std::pow((double)tr->beta2, (double)tr->steps);
-        TGM_LAUNCH(k_adam, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, tr->theta, tr->grad,
-                   tr->m1, tr->m2, n, tr->lr, tr->beta1, tr->beta2, tr->eps, (float)c1,
-                   (float)c2);
+    FinishArgs f{};
+    // the tensors in vector order: the product that gives them, whether its
+    // row sums do, and the tensor's row length
+    const struct {
+        int prob, sums, cols;
+    } src[kNParams] = {{0, 0, D_x}, {1, 0, M}, {0, 1, 1}, {1, 1, 1}, {2, 0, Dq},   {2, 1, 1},
+                       {3, 0, Dkv}, {-1, 0, 1}, {4, 0, Dkv}, {4, 1, 1}, {5, 0, 2 * M}, {5, 1, 1},
+                       {6, 0, M},   {7, 0, M},  {6, 1, 1},   {8, 0, M}, {-1, 0, 1}};
+    for (int k = 0; k < kNParams; ++k) {
+        GradSeg &d = f.seg[k];
+        d.off = tr->off[k];
+        d.cols = d.ld = src[k].cols;
+        if (src[k].prob < 0)
+            continue;
+        const GemmProb &p = w[src[k].prob];
+        d.splits = p.splits;
+        d.part = src[k].sums ? p.colsum : p.C;
+        d.stride = src[k].sums ? p.colsum_stride : p.split_stride;
+        d.rows = p.colsum;
+        d.rows_stride = p.colsum_stride;
+        if (k == 4)
+            d.ld = M;
     }
+    f.n = tr->n_params;
+    f.theta = tr->theta;
+    f.grad = tr->grad;
+    f.m1 = tr->m1;
+    f.m2 = tr->m2;
+    f.omega = m->omega;
+    f.beta = m->beta;
+    f.adam = tr->opt == TGM_OPT_ADAM;
+    f.lr = tr->lr;
+    f.b1 = tr->beta1;
+    f.b2 = tr->beta2;
+    f.eps = tr->eps;
+    f.c1 = (float)(1.0 - std::pow((double)tr->beta1, (double)tr->steps));
+    f.c2 = (float)(1.0 - std::pow((double)tr->beta2, (double)tr->steps));
+    f.lossv = tr->lossv;
+    f.dsc = tr->dsc;
+    f.b = b;
+    f.loss = tr->loss;
+    f.loss_out = loss_out;
+    TGM_LAUNCH(k_grad_finish, dim3((unsigned)cdiv(f.n, 256) + 1), dim3(256), 0, s, f);
     ModelParams mp{W_ih, W_hh, b_ih, b_hh, W_q, b_q, W_k, b_k, W_v, b_v, W_o, b_o};
     return model_repack(m, mp, s);
 }
