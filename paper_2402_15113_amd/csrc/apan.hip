@@ -11,18 +11,17 @@
 // One call per iteration (tgm_apan_step): commit the due write sets, gather
 // the node set's memories and mailboxes, the attention and the GRU, the
 // embeddings, and the staging of the iteration's write set.  The deliveries
-// of an iteration are radix-sorted by (node, delivery index); the index is
+// of an iteration are stably sorted by node; the delivery index is
 // monotone in (t, e, role, slot), so each node's segment is in mail order and
 // its last K entries are the ones its mailbox keeps.
 #include <hip/hip_runtime.h>
-
-#include <hipcub/hipcub.hpp>
 
 #include <algorithm>
 #include <cmath>
 #include <vector>
 
 #include "common.h"
+#include "sort.h"
 
 using namespace tgm;
 
@@ -243,49 +242,47 @@ __global__ __launch_bounds__(256) void k_apan_embed(int R, int M,
 // ------------------------------------------------------------- staging
 // Delivery d = ((k 2 + role)(nb + 1) + slot) of batch event k: the mail of
 // endpoint v (role 0: src, 1: dst) to v (slot 0) or to its neighbour in
-// sampled slot (slot - 1) of root role b + k.  Key (node << 32) | d; empty
-// or unused deliveries get the largest key.
-__global__ __launch_bounds__(256) void k_apan_keys(int32_t b, int nb, int propagate,
+// sampled slot (slot - 1) of root role b + k.  Sort key: the node, or N (past
+// every node) for empty and unused deliveries.
+__global__ __launch_bounds__(256) void k_apan_keys(int32_t b, int nb, int propagate, int32_t N,
                                                    const int32_t *__restrict__ root,
                                                    const int32_t *__restrict__ nbr,
-                                                   const int32_t *__restrict__ cnt,
-                                                   uint64_t *__restrict__ keys)
+                                                   const int32_t *__restrict__ cnt, SortPlan p)
 {
-    const int64_t d = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    __shared__ int32_t count[1 << kSortDigit];
     const int per = nb + 1;
-    if (d >= (int64_t)2 * b * per)
-        return;
-    const int slot = (int)(d % per), kr = (int)(d / per), role = kr & 1, k = kr >> 1;
-    const int r = role * b + k;
-    int32_t w = -1;
-    if (slot == 0)
-        w = root[r];
-    else if (propagate && slot - 1 < cnt[r])
-        w = nbr[(int64_t)r * nb + slot - 1];
-    keys[d] = w < 0 ? ~(uint64_t)0 : ((uint64_t)(uint32_t)w << 32) | (uint64_t)d;
+    sort_keys_tile(p, blockIdx.x, count, [&](int64_t d) {
+        const int slot = (int)(d % per), kr = (int)(d / per), role = kr & 1, k = kr >> 1;
+        const int r = role * b + k;
+        int32_t w = N;
+        if (slot == 0)
+            w = root[r];
+        else if (propagate && slot - 1 < cnt[r])
+            w = nbr[(int64_t)r * nb + slot - 1];
+        return min((uint32_t)w, (uint32_t)N);
+    });
 }
 
 // Segment bounds by node id over the sorted keys
-__global__ __launch_bounds__(256) void k_apan_bounds(int64_t n, const uint64_t *__restrict__ keys,
+__global__ __launch_bounds__(256) void k_apan_bounds(int64_t n, const uint32_t *__restrict__ keys,
                                                      int32_t N, int32_t *__restrict__ seg,
                                                      int32_t *__restrict__ seg_end)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n || keys[i] == ~(uint64_t)0)
+    if (i >= n || keys[i] >= (uint32_t)N)
         return;
-    const int32_t w = (int32_t)(keys[i] >> 32);
-    if (w < 0 || w >= N)
-        return;
-    if (i == 0 || (keys[i - 1] >> 32) != (keys[i] >> 32))
+    const uint32_t w = keys[i];
+    if (i == 0 || keys[i - 1] != w)
         seg[w] = (int32_t)i;
-    if (i == n - 1 || (keys[i + 1] >> 32) != (keys[i] >> 32))
+    if (i == n - 1 || keys[i + 1] != w)
         seg_end[w] = (int32_t)(i + 1);
 }
 
 struct StageArgs2 {
     int32_t b, nb, M, D_e, D_m, K, N;
     int64_t first;
-    const uint64_t *keys;       // sorted
+    const uint32_t *keys;       // sorted
+    const int32_t *dels;        // their deliveries
     const int32_t *seg, *seg_end;
     const int32_t *root_pos;    // [3b]
     const float *s_new, *efeat;
@@ -304,13 +301,12 @@ __global__ __launch_bounds__(256) void k_apan_stage_mail(StageArgs2 a, int64_t n
     const int lane = threadIdx.x & 63;
     if (i >= n)
         return;
-    const uint64_t key = a.keys[i];
-    if (key == ~(uint64_t)0) {
+    if (a.keys[i] >= (uint32_t)a.N) {
         if (lane == 0)
             a.d_keep[i] = 0;
         return;
     }
-    const int32_t w = (int32_t)(key >> 32);
+    const int32_t w = (int32_t)a.keys[i];
     const int64_t lo = a.seg[w], hi = a.seg_end[w];
     const int64_t keep_from = max(lo, hi - a.K);
     if (i < keep_from) {
@@ -318,9 +314,9 @@ __global__ __launch_bounds__(256) void k_apan_stage_mail(StageArgs2 a, int64_t n
             a.d_keep[i] = 0;
         return;
     }
-    const int64_t d = (int64_t)(key & 0xffffffffu);
+    const int d = a.dels[i];
     const int per = a.nb + 1;
-    const int kr = (int)(d / per), role = kr & 1, k = kr >> 1;
+    const int kr = d / per, role = kr & 1, k = kr >> 1;
     const int pv = a.root_pos[role * a.b + k], po = a.root_pos[(1 - role) * a.b + k];
     const int M = a.M, D_e = a.D_e;
     float *row = a.d_mail + i * a.D_m;
@@ -528,10 +524,8 @@ struct tgm_apan {
     double *f_mem_ts = nullptr, *f_mb_ts = nullptr, *t_new = nullptr;
     int32_t *f_ver = nullptr, *f_cnt = nullptr;
     // staging: keys, sort, segments
-    uint64_t *keys = nullptr, *keys_sorted = nullptr;
+    SortBuffers sort;   // deliveries by node
     int32_t *seg = nullptr, *seg_end = nullptr;
-    void *sort_tmp = nullptr;
-    size_t sort_bytes = 0;
     // ring of s + 1 write sets: memory rows by node-set position, mail rows
     // by sorted delivery position
     struct Slot {
@@ -590,11 +584,12 @@ extern "C" tgm_status_t tgm_apan_destroy(tgm_apan_t a)
     void *bufs[] = {a->W_ih, a->W_hh, a->b_ih, a->b_hh, a->W_q, a->b_q, a->W_k, a->b_k,
                     a->omega, a->beta, a->mem, a->mb, a->mem_ts, a->mb_ts, a->ver, a->head,
                     a->cnt, a->f_mem, a->f_mb, a->Xq, a->Q, a->U, a->qb, a->X, a->Gx, a->Gh,
-                    a->f_mem_ts, a->f_mb_ts, a->t_new, a->f_ver, a->f_cnt, a->keys,
-                    a->keys_sorted, a->seg, a->seg_end, a->sort_tmp, a->r_flag, a->r_node,
+                    a->f_mem_ts, a->f_mb_ts, a->t_new, a->f_ver, a->f_cnt, a->seg,
+                    a->seg_end, a->r_flag, a->r_node,
                     a->r_mem, a->r_ts, a->d_node, a->d_rank, a->d_keep, a->d_mail, a->d_t};
     for (void *b : bufs)
         (void)hipFree(b);
+    sort_destroy(&a->sort);
     delete a;
     return TGM_OK;
 }
@@ -665,8 +660,6 @@ extern "C" tgm_status_t tgm_apan_create(const tgm_apan_desc *d, const tgm_weight
     alloc(&a->t_new, C);
     alloc(&a->f_ver, C);
     alloc(&a->f_cnt, C);
-    alloc(&a->keys, MD);
-    alloc(&a->keys_sorted, MD);
     alloc(&a->seg, N);
     alloc(&a->seg_end, N);
     alloc(&a->r_flag, slots * C);
@@ -678,14 +671,11 @@ extern "C" tgm_status_t tgm_apan_create(const tgm_apan_desc *d, const tgm_weight
     alloc(&a->d_keep, slots * MD);
     alloc(&a->d_mail, slots * MD * D_m);
     alloc(&a->d_t, slots * MD);
-    if (st == TGM_OK) {
-        size_t bytes = 0;
-        if (hipcub::DeviceRadixSort::SortKeys(nullptr, bytes, a->keys, a->keys_sorted, (int)MD, 0,
-                                              64) != hipSuccess)
-            st = TGM_EDEVICE;
-        a->sort_bytes = bytes;
-        alloc((char **)&a->sort_tmp, (int64_t)bytes);
-    }
+    if (st == TGM_OK)
+        st = sort_create(&a->sort, MD, N, [&](auto **ptr, int64_t n) {
+            alloc(ptr, n);
+            return st == TGM_OK;
+        });
     hipStream_t s = as_stream(stream);
     if (st == TGM_OK) {
         const struct {
@@ -802,14 +792,14 @@ extern "C" tgm_status_t tgm_apan_step(tgm_apan_t a, tgm_graph_t g, int64_t iter,
                    a->r_flag + r * C, a->r_node + r * C, a->r_mem + r * C * M, a->r_ts + r * C);
     const int64_t n_del = (int64_t)2 * b * (nb + 1);
     if (n_del > 0) {
-        TGM_LAUNCH(k_apan_keys, dim3((unsigned)cdiv(n_del, 256)), dim3(256), 0, s, b, nb,
-                   a->propagate, sb->root, sb->nbr, sb->cnt, a->keys);
-        size_t bytes = a->sort_bytes;
-        TGM_HIP(hipcub::DeviceRadixSort::SortKeys(a->sort_tmp, bytes, a->keys, a->keys_sorted,
-                                                  (int)n_del, 0, 64, s));
+        const SortPlan plan = sort_plan(a->sort, n_del);
+        TGM_LAUNCH(k_apan_keys, dim3((unsigned)sort_tiles(n_del)), dim3(256), 0, s, b, nb,
+                   a->propagate, a->N, sb->root, sb->nbr, sb->cnt, plan);
+        TGM_TRY_STATUS(sort_launch(a->sort, plan, s));
         TGM_LAUNCH(k_apan_bounds, dim3((unsigned)cdiv(n_del, 256)), dim3(256), 0, s, n_del,
-                   a->keys_sorted, a->N, a->seg, a->seg_end);
-        StageArgs2 sa{b, nb, M, a->D_e, D_m, K, a->N, lo, a->keys_sorted, a->seg, a->seg_end,
+                   a->sort.out_keys, a->N, a->seg, a->seg_end);
+        StageArgs2 sa{b, nb, M, a->D_e, D_m, K, a->N, lo, a->sort.out_keys, a->sort.out_vals, a->seg,
+                      a->seg_end,
                       sb->root_pos, mem_new, g->efeat, g->t, a->d_node + r * MD,
                       a->d_rank + r * MD, a->d_keep + r * MD, a->d_mail + r * MD * D_m,
                       a->d_t + r * MD};

@@ -30,13 +30,12 @@
 // of 600: 919 and 229 us.
 #include <hip/hip_runtime.h>
 
-#include <hipcub/hipcub.hpp>
-
 #include <algorithm>
 #include <cmath>
 #include <utility>
 
 #include "common.h"
+#include "sort.h"
 
 using namespace tgm;
 
@@ -104,7 +103,8 @@ __global__ __launch_bounds__(256) void k_pred(PredArgs a)
 }
 
 // ------------------------------------------------------------- attention
-// What the step needs besides its products' outputs, one launch:
+// What the step needs besides its products' outputs, one launch (the keys'
+// workgroups, which take longest, first):
 //   root rows   Xo[r][M .. 2M) = s'_v (the query's and the output
 //               projection's input), one wavefront per root;
 //   node rows   X[p] = [mail || phi(mail_ts - mem_ts)] and Hm[p] = mem[p] of
@@ -121,15 +121,30 @@ struct RowArgs {
     const double *mem_ts, *mail_ts, *omega, *beta;
     const float *s_new, *mem, *mail, *W_q, *b_q;
     float *Xo, *X, *Hm, *cq;
-    uint32_t *keys;
-    int32_t *vals;
+    SortPlan sort;
 };
 
 __global__ __launch_bounds__(256) void k_train_rows(RowArgs a)
 {
+    __shared__ int32_t count[1 << kSortDigit];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int M = a.M, D_m = a.D_m, D_t = a.D_t;
     int blk = blockIdx.x;
+    if (blk < a.n_key) {
+        sort_keys_tile(a.sort, blk, count, [&](int64_t t) {
+            uint32_t key;
+            if (t < a.R) {
+                key = (uint32_t)a.root_pos[t];
+            } else {
+                const int64_t sl = t - a.R;
+                const int r = (int)(sl / a.nb), j = (int)(sl % a.nb);
+                key = j < a.cnt[r] ? (uint32_t)a.nbr_pos[sl] : (uint32_t)a.cap;
+            }
+            return min(key, (uint32_t)a.cap);
+        });
+        return;
+    }
+    blk -= a.n_key;
     if (blk < a.n_root) {
         const int r = blk * 4 + wave;
         if (r < a.R)
@@ -157,24 +172,6 @@ __global__ __launch_bounds__(256) void k_train_rows(RowArgs a)
         return;
     }
     blk -= a.n_node;
-    if (blk < a.n_key) {
-        const int64_t t = (int64_t)blk * 256 + threadIdx.x;
-        const int64_t S = (int64_t)a.R * a.nb;
-        if (t >= a.R + S)
-            return;
-        uint32_t key;
-        if (t < a.R) {
-            key = (uint32_t)a.root_pos[t];
-        } else {
-            const int64_t sl = t - a.R;
-            const int r = (int)(sl / a.nb), j = (int)(sl % a.nb);
-            key = j < a.cnt[r] ? (uint32_t)a.nbr_pos[sl] : (uint32_t)a.cap;
-        }
-        a.keys[t] = min(key, (uint32_t)a.cap);
-        a.vals[t] = (int32_t)t;
-        return;
-    }
-    blk -= a.n_key;
     const int k = blk * 4 + wave;
     if (k >= M)
         return;
@@ -785,11 +782,8 @@ struct tgm_trainer {
     float *alpha = nullptr, *dKm = nullptr, *ds = nullptr;
     float *X = nullptr, *Hm = nullptr, *Gx = nullptr, *Gh = nullptr, *dGx = nullptr,
           *dGh = nullptr;
-    uint32_t *keys = nullptr, *keys_sorted = nullptr;   // node-set positions
-    int32_t *vals = nullptr, *vals_sorted = nullptr;    // contributors
+    SortBuffers sort;   // contributors by node-set position
     float *ds_head = nullptr, *ds_tail = nullptr;       // [sorted blocks x M] open runs
-    void *sort_tmp = nullptr;
-    size_t sort_bytes = 0;
     float *p(int k) const { return theta + off[k]; }
     float *gr(int k) const { return grad + off[k]; }
 };
@@ -799,15 +793,6 @@ namespace {
 // Parts a weight gradient's reduction is cut into at most, and at least the
 // length of a part.
 constexpr int kMaxSplits = 32, kMinSplit = 256, kGradBlocks = 2048;
-
-// Bits that hold the sort keys 0 .. nodes
-int key_bits(int32_t nodes)
-{
-    int bits = 1;
-    while (bits < 31 && (int64_t(1) << bits) <= nodes)
-        ++bits;
-    return bits;
-}
 
 // out = x op(w): the products of the forward pass and of the gradients that
 // go back through it.  x [m x k] (leading dimension ldx).
@@ -888,11 +873,11 @@ extern "C" tgm_status_t tgm_trainer_destroy(tgm_trainer_t tr)
     void *bufs[] = {tr->theta, tr->grad, tr->m1, tr->m2, tr->part, tr->Zs, tr->Zd, tr->dZsrc,
                     tr->dZdst, tr->act, tr->dsc, tr->lossv, tr->loss, tr->cq, tr->Q,
                     tr->Xo, tr->dO, tr->dXo, tr->dQ, tr->U, tr->abar, tr->dbar, tr->alpha,
-                    tr->dKm, tr->ds, tr->X, tr->Hm, tr->Gx, tr->Gh, tr->dGx, tr->dGh, tr->keys,
-                    tr->keys_sorted, tr->vals, tr->vals_sorted, tr->ds_head, tr->ds_tail,
-                    tr->sort_tmp};
+                    tr->dKm, tr->ds, tr->X, tr->Hm, tr->Gx, tr->Gh, tr->dGx, tr->dGh,
+                    tr->ds_head, tr->ds_tail};
     for (void *b : bufs)
         (void)hipFree(b);
+    sort_destroy(&tr->sort);
     delete tr;
     return TGM_OK;
 }
@@ -989,24 +974,13 @@ extern "C" tgm_status_t tgm_trainer_create(tgm_model_t m, const tgm_weights *w,
     alloc(&tr->Gh, C * 3 * M);
     alloc(&tr->dGx, C * 3 * M);
     alloc(&tr->dGh, C * 3 * M);
-    alloc(&tr->keys, n_items);
-    alloc(&tr->keys_sorted, n_items);
-    alloc(&tr->vals, n_items);
-    alloc(&tr->vals_sorted, n_items);
     alloc(&tr->ds_head, blocks * M);
     alloc(&tr->ds_tail, blocks * M);
-    if (st == TGM_OK) {
-        // the sort picks its method by size: room for every size it may get
-        for (int64_t n = n_items; n > 0 && st == TGM_OK; n /= 2) {
-            size_t bytes = 0;
-            if (hipcub::DeviceRadixSort::SortPairs(nullptr, bytes, tr->keys, tr->keys_sorted,
-                                                   tr->vals, tr->vals_sorted, (int)n, 0,
-                                                   key_bits(tr->max_nodes)) != hipSuccess)
-                st = TGM_EDEVICE;
-            tr->sort_bytes = std::max(tr->sort_bytes, bytes);
-        }
-        alloc((char **)&tr->sort_tmp, (int64_t)tr->sort_bytes);
-    }
+    if (st == TGM_OK)
+        st = sort_create(&tr->sort, n_items, C, [&](auto **ptr, int64_t n) {
+            alloc(ptr, n);
+            return st == TGM_OK;
+        });
     if (st != TGM_OK) {
         tgm_trainer_destroy(tr);
         return st;
@@ -1094,9 +1068,9 @@ tgm_status_t tgm::train_step_launch(tgm_trainer_t tr, tgm_model_t m, tgm_graph_t
     float *s_v = tr->Xo + M;   // the roots' new memories, rows of 2M
 
     RowArgs ra{R, nb, M, tr->D_m, tr->D_t, cap, ldx, (int)cdiv(R, 4), (int)cdiv(cap, 4),
-               (int)cdiv(n_items, 256), sb.root_pos, sb.nbr_pos, sb.cnt, sb.n_nodes, fb.ver,
+               (int)sort_tiles(n_items), sb.root_pos, sb.nbr_pos, sb.cnt, sb.n_nodes, fb.ver,
                fb.mem_ts, fb.mail_ts, m->omega, m->beta, mem_new, fb.mem, fb.mail, W_q, b_q,
-               tr->Xo, tr->X, tr->Hm, tr->cq, tr->keys, tr->vals};
+               tr->Xo, tr->X, tr->Hm, tr->cq, sort_plan(tr->sort, n_items)};
     TGM_LAUNCH(k_train_rows,
                dim3((unsigned)(ra.n_root + ra.n_node + ra.n_key + cdiv(M, 4))), dim3(256), 0, s,
                ra);
@@ -1158,15 +1132,12 @@ tgm_status_t tgm::train_step_launch(tgm_trainer_t tr, tgm_model_t m, tgm_graph_t
         TGM_TRY_STATUS(gemm_launch(false, false, &v, 1, s));
     }
     // each node's gradient: its contributors' rows, sorted by node
-    size_t sort_bytes = tr->sort_bytes;
-    TGM_HIP(hipcub::DeviceRadixSort::SortPairs(tr->sort_tmp, sort_bytes, tr->keys,
-                                               tr->keys_sorted, tr->vals, tr->vals_sorted,
-                                               (int)n_items, 0, key_bits(cap), s));
+    TGM_TRY_STATUS(sort_launch(tr->sort, ra.sort, s));
     TGM_LAUNCH(k_ds_block, dim3((unsigned)cdiv(n_items, 256)), dim3(256), 0, s, n_items, cap, M,
-               R, tr->keys_sorted, tr->vals_sorted, tr->dXo, tr->dKm, tr->ds, tr->ds_head,
+               R, tr->sort.out_keys, tr->sort.out_vals, tr->dXo, tr->dKm, tr->ds, tr->ds_head,
                tr->ds_tail);
     TGM_LAUNCH(k_ds_join, dim3((unsigned)cdiv(n_items, 256)), dim3(256), 0, s, n_items, cap, M,
-               tr->keys_sorted, tr->ds_head, tr->ds_tail, tr->ds);
+               tr->sort.out_keys, tr->ds_head, tr->ds_tail, tr->ds);
     // memory updater (GRU) backward
     TGM_LAUNCH(k_gru_bwd, dim3((unsigned)cdiv((int64_t)cap * M, 256)), dim3(256), 0, s,
                sb.n_nodes, cap, M, fb.ver, tr->Gx, tr->Gh, tr->Hm, tr->ds, tr->dGx, tr->dGh);
