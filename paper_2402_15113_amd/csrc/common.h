@@ -338,6 +338,23 @@ __device__ __forceinline__ int64_t recent_end(const int64_t *__restrict__ off,
     return ws + __popcll(__ballot(below));
 }
 
+// Sum over the wavefront, the same value in every lane: the 16-lane rows with
+// DPP moves, then the four row sums through scalar registers (no LDS).
+__device__ __forceinline__ float wave_total(float v)
+{
+    const int x = __float_as_int(row16_sum(v));
+    const float a = __int_as_float(__builtin_amdgcn_readlane(x, 0)) +
+                    __int_as_float(__builtin_amdgcn_readlane(x, 16));
+    const float b = __int_as_float(__builtin_amdgcn_readlane(x, 32)) +
+                    __int_as_float(__builtin_amdgcn_readlane(x, 48));
+    return a + b;
+}
+
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
 __device__ __forceinline__ float wave_sum(float v)
 {
 #pragma unroll

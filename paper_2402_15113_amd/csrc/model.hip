@@ -2176,25 +2176,44 @@ __global__ __launch_bounds__(512) void k_attn_fold_gather(AttnArgs g, int n_attn
 //   4. output GEMM h = ReLU(W_o [o || s'_r] + b_o).
 // LDS: 2 x 16 rows of the slot-row width and 16 rows of [o || s'_r], about
 // 53 KB at the GDELT-shaped sizes, so that two workgroups share a CU.
-constexpr int kAggCols = 5;     // slot-row columns per lane (KF <= 320)
-constexpr int kAggTCols = 2;    // of them time codes (D_t <= 128)
+constexpr int kAggMaxKF = 320;  // slot-row width
+constexpr int kAggTCols = 2;    // time codes per lane (D_t <= 128)
 constexpr int kAggDC = 7;       // 16-wide chunks of M (M <= 112)
 constexpr int kAggUT = 3;       // U tiles per wave (KFC <= 24)
 constexpr int kAggMaxH = 4;
 constexpr int kAggMaxKC = 24;   // k-chunks of the value GEMM (KFC) and of the output one (OC)
 constexpr int kAggRing = 8;     // weight chunks in flight per wave in those GEMMs
 
-// Sum over the wavefront, the same in every lane: DPP sums inside each 16-lane
-// row, then the four row sums (lanes 0, 16, 32, 48) read as scalars and added
-// in that order.
-__device__ __forceinline__ float wave_sum_rows(float v)
+// The sums over the wavefront of 2 NJ values at once (v[j][e], e < 2): each
+// exchange folds two registers into one, so the 20 scores of a root with 10
+// slots and two heads take 50 instructions instead of about 300 with a
+// reduction each.  y[m] holds, in every lane of 16-lane row i, the sum of
+// v[2 m + (i & 1)][i >> 1].
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+template <int NJ>
+__device__ __forceinline__ void wave_sums(const float (&v)[NJ][2], float (&y)[NJ / 2])
 {
-    v = row16_sum(v);
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return (r0 + r1) + (r2 + r3);
+    float x[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {   // halves: lanes 0-31 hold v[j][0], 32-63 v[j][1]
+        const u2 s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[j][0]),
+                                                      __float_as_uint(v[j][1]), false, false);
+        x[j] = __uint_as_float(s.x) + __uint_as_float(s.y);
+    }
+#pragma unroll
+    for (int m = 0; m < NJ / 2; ++m) {   // rows: even ones hold x[2 m], odd ones x[2 m + 1]
+        const u2 s = __builtin_amdgcn_permlane16_swap(
+            __float_as_uint(x[2 * m]), __float_as_uint(x[2 * m + 1]), false, false);
+        y[m] = row16_sum(__uint_as_float(s.x) + __uint_as_float(s.y));
+    }
+}
+
+// x of the lane's row and of the row it is paired with (0 and 1, 2 and 3)
+__device__ __forceinline__ f2 row_pair(float x)
+{
+    const u2 s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false,
+                                                  false);
+    return f2{__uint_as_float(s.x), __uint_as_float(s.y)};
 }
 
 // One GEMM of a 16-row A block in LDS (k-chunks of 16 columns) against packed
@@ -2232,7 +2251,9 @@ __device__ __forceinline__ void agg_ring_load(const f4 *pw, int64_t bstep, int K
         ring[i] = pw[min(i, KC - 1) * bstep];
 }
 
-template <int NBM>   // slots per root held in registers (nb <= NBM)
+// NBM: slots per root held in registers (nb <= NBM, even); CE: 64-wide groups
+// of edge features (D_e <= 64 CE)
+template <int NBM, int CE>
 __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, int bid)
 {
     const int RT = g.RT;
@@ -2357,114 +2378,179 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
         }
     }
     // 1e. the own root's slot rows: edge features (HBM), then the time codes
-    // phi(t_root - t_slot) computed while those are in flight
-    float xs[NBM][kAggCols];   // slot j's columns lane + 64 i
+    // phi(t_root - t_slot) computed while those are in flight.  Every load is
+    // unconditional, at clamped columns and events: with a condition per
+    // element (200 of them) and a reduction per score a wavefront issued 3,100
+    // vector instructions instead of 1,900 (113.5 against 110 us for 12,000
+    // roots with the node projections, 19.4 against 16.6 us for 600 small
+    // ones; touching the rows' lines earlier gained nothing).
+    constexpr int CT = kAggTCols, CX = CE + CT;
+    float xs[NBM][CX];   // slot j's edge features lane + 64 i, then its time codes
+    const int cu = __builtin_amdgcn_readfirstlane(c);
+    if (D_e > 0) {
 #pragma unroll
-    for (int j = 0; j < NBM; ++j) {
-        // the slot's event id, the same in every lane (a scalar base address)
-        const int ej = __builtin_amdgcn_readfirstlane(__shfl(my_e, j, kWave));
-        const float *erow = g.efeat + (int64_t)max(ej, 0) * D_e - D_t;
+        for (int j = 0; j < NBM; ++j) {
+            const float *erow =
+                g.efeat + (int64_t)max(__builtin_amdgcn_readlane(my_e, j), 0) * D_e;
 #pragma unroll
-        for (int i = 0; i < kAggCols; ++i) {
-            const int k = lane + kWave * i;
-            float x = 0.f;
-            if (j < c && ej >= 0 && k >= D_t && k < KF)
-                x = erow[k];
-            xs[j][i] = x;
+            for (int i = 0; i < CE; ++i)
+                xs[j][i] = erow[min(lane + kWave * i, D_e - 1)];
         }
+    } else {
+#pragma unroll
+        for (int j = 0; j < NBM; ++j)
+#pragma unroll
+            for (int i = 0; i < CE; ++i)
+                xs[j][i] = 0.f;
     }
     issue_fence();
     {
-        double om[kAggTCols], be[kAggTCols];
+        const long long dti = __double_as_longlong(my_dt);
+        const int dlo = (int)dti, dhi = (int)(dti >> 32);
 #pragma unroll
-        for (int i = 0; i < kAggTCols; ++i) {
-            const int k = min(lane + kWave * i, max(D_t - 1, 0));
-            om[i] = D_t > 0 ? g.omega[k] : 0.0;
-            be[i] = D_t > 0 ? g.beta[k] : 0.0;
-        }
+        for (int i = 0; i < CT; ++i) {
+            if (kWave * i >= D_t) {
 #pragma unroll
-        for (int j = 0; j < NBM; ++j) {
-            const double dtj = __shfl(my_dt, j, kWave);
+                for (int j = 0; j < NBM; ++j)
+                    xs[j][CE + i] = 0.f;
+                continue;
+            }
+            const int k = min(lane + kWave * i, D_t - 1);
+            const double om = g.omega[k], be = g.beta[k];
 #pragma unroll
-            for (int i = 0; i < kAggTCols; ++i)
-                if (lane + kWave * i < D_t)
-                    xs[j][i] = j < c ? time_enc(om[i], be[i], dtj) : 0.f;
+            for (int j = 0; j < NBM; ++j) {
+                const unsigned l = (unsigned)__builtin_amdgcn_readlane(dlo, j);
+                const long long h = __builtin_amdgcn_readlane(dhi, j);
+                xs[j][CE + i] = time_enc(om, be, __longlong_as_double((h << 32) | l));
+            }
         }
     }
+    // a filled slot whose event id is out of range has no edge features
+    if (D_e > 0 && __ballot(lane < cu && my_e < 0) != 0)
+#pragma unroll
+        for (int j = 0; j < NBM; ++j)
+            if (__builtin_amdgcn_readlane(my_e, j) < 0)
+#pragma unroll
+                for (int i = 0; i < CE; ++i)
+                    xs[j][i] = 0.f;
     __syncthreads();
 
-    // 2. scores, softmax, aggregates (own root); the value seeds of the lane's
-    // columns d = lane, lane + 64 and s'_r load first
+    // 2. scores, softmax, aggregates (own root), two heads at a time; the value
+    // seeds of the lane's columns d = lane, lane + 64 and s'_r load first
     const float scale = 1.0f / sqrtf((float)d_h);
     f4 ring[kAggRing];
     if (own) {
-        float vs[NBM][2];
+        float vs[NBM][2], sr_[2];
 #pragma unroll
-        for (int j = 0; j < NBM; ++j) {
-            const int npj = __shfl(my_np, j, kWave);
+        for (int j = 0; j < NBM; ++j) {   // a slot without a node reads the bias row
+            const int npj = __builtin_amdgcn_readlane(my_np, j);
             const float *vrow = (npj >= 0 ? g.P + (int64_t)npj * g.ldP : g.pbias) + 2 * M;
 #pragma unroll
             for (int u = 0; u < 2; ++u)
-                vs[j][u] = (j < c && lane + kWave * u < M) ? vrow[lane + kWave * u] : 0.f;
+                vs[j][u] = vrow[min(lane + kWave * u, M - 1)];
         }
-        float sr_[2];
+        {
+            const bool ok = __builtin_amdgcn_readfirstlane(pv_ok);
+            const float *srow = g.mem_new + (int64_t)(ok ? pv : 0) * M;
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-            sr_[u] = (pv_ok && lane + kWave * u < M) ? g.mem_new[(int64_t)pv * M + lane + kWave * u]
-                                                      : 0.f;
+            for (int u = 0; u < 2; ++u)
+                sr_[u] = srow[min(lane + kWave * u, M - 1)];
+            if (!ok)
+                sr_[0] = sr_[1] = 0.f;
+        }
         issue_fence();
         float sv[2] = {0.f, 0.f};   // sum_j alpha_j,head(d) seedV_j[d]
+        const int row = lane >> 4;
+        for (int e0 = 0; e0 < H; e0 += 2) {
+            // the pair's U columns, zero past the widths and past the last head
+            float uu[2][CX];
 #pragma unroll
-        for (int eta = 0; eta < kAggMaxH; ++eta) {
-            if (eta < H) {
-                float uu[kAggCols];
+            for (int e = 0; e < 2; ++e) {
+                const float *us = Us + (wave * H + min(e0 + e, H - 1)) * KFP;
 #pragma unroll
-                for (int i = 0; i < kAggCols; ++i)
-                    uu[i] = lane + kWave * i < KFC * 16
-                                ? Us[(wave * H + eta) * KFP + lane + kWave * i] : 0.f;
-                float al[NBM];
-                float mx = -INFINITY;
-#pragma unroll
-                for (int j = 0; j < NBM; ++j) {
-                    float part = 0.f;
-#pragma unroll
-                    for (int i = 0; i < kAggCols; ++i)
-                        part = fmaf(xs[j][i], uu[i], part);
-                    const float seed = Sk[(wave * nb + min(j, nb - 1)) * H + eta];
-                    const float scj = (wave_sum_rows(part) + seed) * scale;
-                    al[j] = j < c ? scj : -INFINITY;
-                    mx = fmaxf(mx, al[j]);
-                }
-                float den = 0.f;
-#pragma unroll
-                for (int j = 0; j < NBM; ++j) {
-                    al[j] = j < c ? __expf(al[j] - mx) : 0.f;
-                    den += al[j];
-                }
-                const float inv = c > 0 ? 1.0f / den : 0.f;   // no slots: no weights
-#pragma unroll
-                for (int j = 0; j < NBM; ++j)
-                    al[j] *= inv;
-                // abar_eta over the lane's columns (zero past KF: xs is)
-#pragma unroll
-                for (int i = 0; i < kAggCols; ++i) {
-                    float a = 0.f;
-#pragma unroll
-                    for (int j = 0; j < NBM; ++j)
-                        a = fmaf(al[j], xs[j][i], a);
-                    if (lane + kWave * i < KFC * 16)
-                        As[(wave * H + eta) * KFP + lane + kWave * i] = a;
+                for (int i = 0; i < CE; ++i) {
+                    const float x = us[min(D_t + lane + kWave * i, KF - 1)];
+                    uu[e][i] = lane + kWave * i < D_e && e0 + e < H ? x : 0.f;
                 }
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int d = lane + kWave * u;
-                    if (d < M && d / d_h == eta) {
-#pragma unroll
-                        for (int j = 0; j < NBM; ++j)
-                            sv[u] = fmaf(al[j], vs[j][u], sv[u]);
-                    }
+                for (int i = 0; i < CT; ++i) {
+                    const float x = us[min(lane + kWave * i, KF - 1)];
+                    uu[e][CE + i] = lane + kWave * i < D_t && e0 + e < H ? x : 0.f;
                 }
             }
+            float part[NBM][2];
+#pragma unroll
+            for (int j = 0; j < NBM; ++j)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    part[j][e] = 0.f;
+#pragma unroll
+                    for (int i = 0; i < CX; ++i)
+                        part[j][e] = fmaf(xs[j][i], uu[e][i], part[j][e]);
+                }
+            // al[m]: in row i, the weight of slot 2 m + (i & 1) for head e0 + (i >> 1)
+            float al[NBM / 2], mx = -INFINITY, den = 0.f;
+            wave_sums<NBM>(part, al);
+#pragma unroll
+            for (int m = 0; m < NBM / 2; ++m) {
+                const int j = 2 * m + (row & 1);
+                const float seed = Sk[(wave * nb + min(j, nb - 1)) * H + min(e0 + (row >> 1), H - 1)];
+                al[m] = j < cu ? (al[m] + seed) * scale : -INFINITY;
+                mx = fmaxf(mx, al[m]);
+            }
+            const f2 mp = row_pair(mx);
+            mx = fmaxf(mp.x, mp.y);
+#pragma unroll
+            for (int m = 0; m < NBM / 2; ++m) {
+                al[m] = 2 * m + (row & 1) < cu ? __expf(al[m] - mx) : 0.f;
+                den += al[m];
+            }
+            const f2 dp = row_pair(den);
+            const float inv = cu > 0 ? 1.0f / (dp.x + dp.y) : 0.f;   // no slots: no weights
+#pragma unroll
+            for (int m = 0; m < NBM / 2; ++m)
+                al[m] *= inv;
+            // abar and the value seeds' sums over the lane's columns
+            float ab[2][CX], sh[2][2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+#pragma unroll
+                for (int i = 0; i < CX; ++i)
+                    ab[e][i] = 0.f;
+                sh[e][0] = sh[e][1] = 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < NBM; ++j)
+                if (j < cu) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const float w = lane_value(al[j / 2], 16 * (2 * e + (j & 1)));
+#pragma unroll
+                        for (int i = 0; i < CX; ++i)
+                            ab[e][i] = fmaf(w, xs[j][i], ab[e][i]);
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+                            sh[e][u] = fmaf(w, vs[j][u], sh[e][u]);
+                    }
+                }
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                if (e0 + e < H) {
+                    float *as = As + (wave * H + e0 + e) * KFP;
+#pragma unroll
+                    for (int i = 0; i < CE; ++i)
+                        if (lane + kWave * i < D_e)
+                            as[D_t + lane + kWave * i] = ab[e][i];
+#pragma unroll
+                    for (int i = 0; i < CT; ++i)
+                        if (lane + kWave * i < D_t)
+                            as[lane + kWave * i] = ab[e][CE + i];
+                    if (KF + lane < KFC * 16)   // the chunks' zero padding
+                        as[KF + lane] = 0.f;
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        sv[u] = (lane + kWave * u) / d_h == e0 + e ? sh[e][u] : sv[u];
+                }
         }
         // [sum alpha seedV || s'_r || 0]
 #pragma unroll
@@ -2520,22 +2606,22 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
     }
 }
 
-template <int NBM>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 ? 4 : 2))) void k_attn_agg(AttnArgs g)
+template <int NBM, int CE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 && CE <= 3 ? 4 : 2))) void k_attn_agg(AttnArgs g)
 {
     extern __shared__ float lds[];
-    attn_agg_block<NBM>(g, lds, blockIdx.x);
+    attn_agg_block<NBM, CE>(g, lds, blockIdx.x);
 }
 
 // with the gather of the next iteration's fetch on the blocks past n_attn
 // (dispatched last: they take the CUs the attention's tail leaves free)
-template <int NBM>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 ? 4 : 2))) void k_attn_agg_gather(
+template <int NBM, int CE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 && CE <= 3 ? 4 : 2))) void k_attn_agg_gather(
     AttnArgs g, int n_attn, GatherPlan gp)
 {
     extern __shared__ float lds[];
     if ((int)blockIdx.x < n_attn) {
-        attn_agg_block<NBM>(g, lds, blockIdx.x);
+        attn_agg_block<NBM, CE>(g, lds, blockIdx.x);
         return;
     }
     gather_blocks(gp, (int)blockIdx.x - n_attn, (int)gridDim.x - n_attn, blockDim.x >> 6,
@@ -2570,10 +2656,12 @@ __global__ __launch_bounds__(256) void k_fold_q_bias(int M, int D_t, const float
 bool attn_lds_opt_in(int bytes, int fold_bytes, int agg_bytes)
 {
     if (agg_bytes > 0) {
-        const void *fa[] = {(const void *)k_attn_agg<4>, (const void *)k_attn_agg<10>,
-                            (const void *)k_attn_agg<16>, (const void *)k_attn_agg_gather<4>,
-                            (const void *)k_attn_agg_gather<10>,
-                            (const void *)k_attn_agg_gather<16>};
+        const void *fa[] = {
+            (const void *)k_attn_agg<4, 3>, (const void *)k_attn_agg<10, 3>,
+            (const void *)k_attn_agg<16, 3>, (const void *)k_attn_agg<10, 4>,
+            (const void *)k_attn_agg<16, 4>, (const void *)k_attn_agg_gather<4, 3>,
+            (const void *)k_attn_agg_gather<10, 3>, (const void *)k_attn_agg_gather<16, 3>,
+            (const void *)k_attn_agg_gather<10, 4>, (const void *)k_attn_agg_gather<16, 4>};
         for (const void *f : fa)
             if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, agg_bytes) !=
                 hipSuccess)
@@ -2681,7 +2769,7 @@ bool attn_agg_fits(const tgm_model *m)
 {
     const int KF = m->D_e + m->D_t;
     return m->nb >= 1 && m->nb <= 16 && m->M % 4 == 0 && m->M <= 112 && m->H >= 1 &&
-           m->H <= kAggMaxH && m->M % m->H == 0 && KF >= 1 && KF <= kAggCols * kWave &&
+           m->H <= kAggMaxH && m->M % m->H == 0 && KF >= 1 && KF <= kAggMaxKF &&
            m->D_t <= kAggTCols * kWave && m->KFC <= kAggUT * kMaxWaves &&
            m->VNB <= kMaxWaves && m->ONB <= kMaxWaves && m->DC <= kAggDC &&
            m->OC <= kAggMaxKC && m->KFC <= kAggMaxKC &&
@@ -3157,23 +3245,30 @@ tgm_status_t launch_attn(const tgm_model *m, const AttnArgs &a, const GatherPlan
     const dim3 block(64 * kMaxWaves);
     if (m->agg) {
         const size_t lds = attn_agg_lds(m);
-        const int nbm = a.nb <= 4 ? 4 : a.nb <= 10 ? 10 : 16;
-        if (next && next->cap > 0) {
-            // one gather block per CU after the attention's blocks
-            const dim3 grid(n_attn + kCUs);
-            switch (nbm) {
-            case 4: TGM_LAUNCH(k_attn_agg_gather<4>, grid, block, lds, s, a, n_attn, *next); break;
-            case 10: TGM_LAUNCH(k_attn_agg_gather<10>, grid, block, lds, s, a, n_attn, *next); break;
-            default: TGM_LAUNCH(k_attn_agg_gather<16>, grid, block, lds, s, a, n_attn, *next); break;
-            }
-            return TGM_OK;
-        }
-        const dim3 grid(n_attn);
-        switch (nbm) {
-        case 4: TGM_LAUNCH(k_attn_agg<4>, grid, block, lds, s, a); break;
-        case 10: TGM_LAUNCH(k_attn_agg<10>, grid, block, lds, s, a); break;
-        default: TGM_LAUNCH(k_attn_agg<16>, grid, block, lds, s, a); break;
-        }
+        // the registers' slot rows: up to 4, 10 or 16 slots of up to 192 edge
+        // features, or 10 or 16 of up to 256
+        const bool ride = next && next->cap > 0;
+        // one gather block per CU after the attention's blocks
+        const dim3 grid(n_attn + (ride ? kCUs : 0));
+#define TGM_AGG(NBM, CE)                                                                       \
+    do {                                                                                       \
+        if (ride)                                                                              \
+            TGM_LAUNCH((k_attn_agg_gather<NBM, CE>), grid, block, lds, s, a, n_attn, *next);   \
+        else                                                                                   \
+            TGM_LAUNCH((k_attn_agg<NBM, CE>), grid, block, lds, s, a);                         \
+    } while (0)
+        const bool narrow = m->D_e <= 3 * kWave;
+        if (narrow && a.nb <= 4)
+            TGM_AGG(4, 3);
+        else if (narrow && a.nb <= 10)
+            TGM_AGG(10, 3);
+        else if (narrow)
+            TGM_AGG(16, 3);
+        else if (a.nb <= 10)
+            TGM_AGG(10, 4);
+        else
+            TGM_AGG(16, 4);
+#undef TGM_AGG
         return TGM_OK;
     }
     const size_t lds = m->fold ? attn_fold_lds(m) : attn_lds(m);

@@ -183,29 +183,12 @@ __global__ __launch_bounds__(256) void k_train_rows(RowArgs a)
         a.cq[k] = acc + a.b_q[k];
 }
 
-// Sum over the wavefront, the same value in every lane: the 16-lane rows with
-// DPP moves, then the four row sums through scalar registers (no LDS).
-__device__ __forceinline__ float wave_total(float v)
-{
-    const int x = __float_as_int(row16_sum(v));
-    const float a = __int_as_float(__builtin_amdgcn_readlane(x, 0)) +
-                    __int_as_float(__builtin_amdgcn_readlane(x, 16));
-    const float b = __int_as_float(__builtin_amdgcn_readlane(x, 32)) +
-                    __int_as_float(__builtin_amdgcn_readlane(x, 48));
-    return a + b;
-}
-
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
         v = fmaxf(v, __shfl_xor(v, o, kWave));
     return v;
-}
-
-__device__ __forceinline__ float lane_of(float v, int l)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
 struct AttArgs {
@@ -404,7 +387,7 @@ __global__ __launch_bounds__(256) void k_att_fwd(AttArgs a)
 #pragma unroll
                 for (int j = 0; j < NC; ++j)
                     if (j < nj)
-                        acc.axpy(lane_of(al, j0 + j), rows.x[j]);
+                        acc.axpy(lane_value(al, j0 + j), rows.x[j]);
             }
         }
         acc.store_cols(a.abar + o, a, lane);
@@ -461,7 +444,7 @@ __global__ __launch_bounds__(256) void k_att_bwd(AttArgs a)
 #pragma unroll
                 for (int j = 0; j < NC; ++j)
                     if (j < nj) {
-                        const float w = lane_of(dsc, j0 + j), aj = lane_of(al, j0 + j);
+                        const float w = lane_value(dsc, j0 + j), aj = lane_value(al, j0 + j);
                         acc.axpy(w, rows.x[j]);
                         float g[2];
 #pragma unroll
