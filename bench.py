@@ -376,32 +376,27 @@ def apan_work_model(wl, K, rows):
     R, n_U, n_mail, n_mails, b = avg("R"), avg("n_U"), avg("n_mail"), avg("n_mails"), avg("b")
     f, d = 4, 8
     n_del = 2 * b * (nb + 1)   # delivery slots; at most K kept per node
-    gemms = [(n_mail, M, M + D_t), (n_mail, D_x, M), (n_mail, 3 * M, D_x), (n_mail, 3 * M, M)]
+    gemms = [(n_mail, D_x, M), (n_mail, 3 * M, D_x), (n_mail, 3 * M, M)]   # in two launches
     return {
-        # the node set's memories, times, versions, counts, heads; every mail
-        # and its time, in and out
-        "k_apan_gather": dict(flops=0, bytes=n_U * (2 * M * f + 2 * (d + 4) + 3 * 4)
-                              + n_mails * 2 * (D_m * f + d)),
-        "k_apan_query_rows": dict(flops=0, bytes=n_U * (M * f + (M + D_t) * f)),
-        "k_gemm": dict(flops=sum(2.0 * a * b_ * c for a, b_, c in gemms) / len(gemms),
-                       bytes=sum(f * (a * c + c * b_ + a * b_) for a, b_, c in gemms)
-                       / len(gemms)),
-        "k_apan_qb": dict(flops=n_U * 2 * M, bytes=n_U * (M + 1) * f),
-        # per mail: its row and time, the score over [mail || phi]; the weighted sum
+        # the node set's memories, times, versions and counts, in and out
+        "k_apan_gather": dict(flops=0, bytes=n_U * (2 * M * f + 2 * (d + 4) + 2 * 4)),
+        "k_gemm": dict(flops=sum(2.0 * a * b_ * c for a, b_, c in gemms) / 2,
+                       bytes=sum(f * (a * c + c * b_ + a * b_) for a, b_, c in gemms) / 2),
+        # per mail: its row and time, in and out, the score over [mail || phi]
+        # and the weighted sum; u and the GRU's row per node
         "k_apan_attn": dict(flops=n_mails * (2 * D_x + 2 * D_m),
-                            bytes=n_mail * (2 * D_x * f + 2 * d + 4 + f)
-                            + n_mails * (D_m * f + d)),
+                            bytes=n_mail * (2 * D_x * f + 2 * d + 4)
+                            + n_mails * 2 * (D_m * f + d)),
         "k_apan_gru": dict(flops=n_mail * 12 * M, bytes=n_U * (2 * M * f + 4)
                            + n_mail * 6 * M * f),
-        "k_apan_embed": dict(flops=0, bytes=R * (2 * M * f + 4)),
-        "k_apan_stage_mem": dict(flops=0, bytes=2 * b * (2 * M * f + 4 + 4 + d + 4)),
-        "k_apan_keys": dict(flops=0, bytes=n_del * 8 + 2 * b * (4 + 4) + 2 * b * nb * 4),
-        "k_apan_bounds": dict(flops=0, bytes=n_del * 8),
+        # the deliveries' keys, the embeddings, the endpoints' memory rows
+        "k_apan_after": dict(flops=0, bytes=n_del * 4 + 2 * b * (4 + 4) + 2 * b * nb * 4
+                             + R * (2 * M * f + 4) + 2 * b * (2 * M * f + 4 + 4 + d + 4)),
         # kept mails (at most K per node): two memory rows, the event's features
         "k_apan_stage_mail": dict(flops=0, bytes=n_del * 8 + min(n_del, K * n_U)
                                   * (2 * (2 * M + D_e) * f + 3 * 4 + d)),
-        "k_apan_commit_mem": dict(flops=0, bytes=2 * b * (2 * M * f + 2 * d + 4)),
-        "k_apan_commit_mail": dict(flops=0, bytes=min(n_del, K * n_U) * (2 * D_m * f + 2 * d)),
+        "k_apan_commit": dict(flops=0, bytes=2 * b * (2 * M * f + 2 * d + 4)
+                              + min(n_del, K * n_U) * (2 * D_m * f + 2 * d)),
     }
 
 

@@ -29,7 +29,7 @@ namespace {
 
 constexpr int kApanMaxK = 16;
 
-struct ApanRows {   // the node set's rows and the staging work space
+struct ApanRows {   // the node set's rows
     const int32_t *nodes, *n_nodes;
     int cap, M, D_m, D_t, K;
     const float *mem, *mb;          // tables [N x M], [N x K x D_m]
@@ -38,165 +38,197 @@ struct ApanRows {   // the node set's rows and the staging work space
     float *f_mem, *f_mb;            // fetched [cap x M], [cap x K x D_m] (oldest first)
     double *f_mem_ts, *f_mb_ts;     // [cap], [cap x K]
     int32_t *f_ver, *f_cnt;         // [cap]
+    int32_t *flag;                  // staging flags of the iteration's slot [n_flag]
+    int n_flag, n_gather;           // workgroups of the gather
+    // attention
+    const float *u;                 // [cap x D_x]
+    const double *omega, *beta;
+    float scale;
+    float *X;                       // [cap x D_x]
+    double *t_new, *new_ts;         // [cap]; new_ts may be null
 };
 
-// Gather of the node set, one wavefront per node: memory, its time and
-// version, and the mailbox's mails oldest first.
+// Gather of the node set's memory rows, times, versions and mail counts, one
+// wavefront per node; the workgroups past n_gather clear the staging flags.
 __global__ __launch_bounds__(256) void k_apan_gather(ApanRows a)
 {
-    const int p = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    const int n = min(*a.n_nodes, a.cap);
-    if (p >= n)
+    if ((int)blockIdx.x >= a.n_gather) {
+        const int i = ((int)blockIdx.x - a.n_gather) * 256 + threadIdx.x;
+        if (i < a.n_flag)
+            a.flag[i] = 0;
         return;
-    const int v = a.nodes[p], M = a.M, D_m = a.D_m, K = a.K;
-    wave_copy_row(a.f_mem + (int64_t)p * M, a.mem + (int64_t)v * M, M, lane);
-    const int cnt = a.mb_cnt[v], head = a.mb_head[v];
-    for (int j = 0; j < cnt; ++j) {
-        const int slot = ((head - cnt + j) % K + K) % K;
-        wave_copy_row(a.f_mb + ((int64_t)p * K + j) * D_m, a.mb + ((int64_t)v * K + slot) * D_m,
-                      D_m, lane);
-        if (lane == 0)
-            a.f_mb_ts[(int64_t)p * K + j] = a.mb_ts[(int64_t)v * K + slot];
     }
+    const int p = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (p >= min(*a.n_nodes, a.cap))
+        return;
+    const int v = a.nodes[p], M = a.M;
+    wave_copy_row(a.f_mem + (int64_t)p * M, a.mem + (int64_t)v * M, M, lane);
     if (lane == 0) {
         a.f_mem_ts[p] = a.mem_ts[v];
         a.f_ver[p] = a.ver[v];
-        a.f_cnt[p] = cnt;
+        a.f_cnt[p] = a.mb_cnt[v];
     }
 }
 
-// Xq[p] = [f_mem[p] || phi(0)], one wavefront per node (rows past n zero)
-__global__ __launch_bounds__(256) void k_apan_query_rows(const int32_t *__restrict__ n_nodes,
-                                                         int cap, int M, int D_t,
-                                                         const float *__restrict__ f_mem,
-                                                         const double *__restrict__ omega,
-                                                         const double *__restrict__ beta,
-                                                         float *__restrict__ Xq)
-{
-    const int p = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    if (p >= cap)
-        return;
-    float *x = Xq + (int64_t)p * (M + D_t);
-    if (p >= min(*n_nodes, cap)) {
-        for (int k = lane; k < M + D_t; k += kWave)
-            x[k] = 0.f;
-        return;
-    }
-    for (int k = lane; k < M; k += kWave)
-        x[k] = f_mem[(int64_t)p * M + k];
-    for (int d = lane; d < D_t; d += kWave)
-        x[M + d] = time_enc(omega[d], beta[d], 0.0);
-}
-
-// The mailbox attention, one wavefront per node with mail: u = W_k^t q has
-// been formed for the node (u [cap x (D_m + D_t)], qb = q . b_k), so the
-// score of mail j is (u . [mail_j || phi(t_newest - t_j)] + qb) / sqrt(M).
-// Writes the GRU input row X[p] = [sum_j alpha_j mail_j || phi(t_newest -
-// mem_ts)] and t_newest; nodes without mail get a zero row.
-struct AttnArgs2 {
-    const int32_t *n_nodes;
-    int cap, M, D_m, D_t, K;
-    float scale;
-    const float *u, *qb, *f_mb;
-    const double *f_mb_ts, *f_mem_ts, *omega, *beta;
-    const int32_t *f_cnt;
-    float *X;          // [cap x (D_m + D_t)]
-    double *t_new;     // [cap]
-};
-
-__global__ __launch_bounds__(256) void k_apan_attn(AttnArgs2 a)
+// The fetch of the mailboxes and the attention over them, one wavefront per
+// node.  u = W_k^t q has been formed for the node, so the score of mail j is
+// u . [mail_j || phi(t_newest - t_j)] / sqrt(M); q . b_k shifts all of a
+// node's scores alike, which the softmax ignores.  Writes the mails oldest
+// first (f_mb, f_mb_ts), t_newest and the GRU's input row X[p] = [sum_j
+// alpha_j mail_j || phi(t_newest - mem_ts)]; a node without mail gets no row
+// (the GRU keeps its memory).
+//
+// A node's mails stay in the wavefront's registers (lane l holds columns l +
+// 64 i of each) from their one load to their copy and their weighted sum.  As
+// a copy to f_mb and an attention that read f_mb twice the two launches took
+// 65 us at a batch of 1,000 (2,800 nodes, 32 MB of mails); this one 16 us.
+template <int NC, int CD>   // K <= NC, D_m <= 64 CD
+__global__ __launch_bounds__(256) void k_apan_attn(ApanRows a)
 {
     const int p = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
     if (p >= a.cap)
         return;
     const int D_m = a.D_m, D_t = a.D_t, D_x = D_m + D_t, K = a.K;
-    float *x = a.X + (int64_t)p * D_x;
-    const int cnt = p < min(*a.n_nodes, a.cap) ? a.f_cnt[p] : 0;
+    const bool in = p < min(*a.n_nodes, a.cap);
+    const int v = in ? a.nodes[p] : 0;
+    const int cnt = in ? __builtin_amdgcn_readfirstlane(a.mb_cnt[v]) : 0;
     if (cnt == 0) {
-        for (int k = lane; k < D_x; k += kWave)
-            x[k] = 0.f;
-        if (lane == 0)
-            a.t_new[p] = p < min(*a.n_nodes, a.cap) ? a.f_mem_ts[p] : 0.0;
+        if (lane == 0) {
+            const double t = in ? a.mem_ts[v] : 0.0;
+            a.t_new[p] = t;
+            if (a.new_ts)
+                a.new_ts[p] = t;
+        }
         return;
     }
-    const float *u = a.u + (int64_t)p * D_x;
-    const float *rows = a.f_mb + (int64_t)p * K * D_m;
-    const double *ts = a.f_mb_ts + (int64_t)p * K;
-    const double tref = ts[cnt - 1];
-    // every mail's partial score at once: per element of u, the loads of all
-    // the node's mails are in flight together (each lane sums its elements
-    // in the same order as a mail-by-mail loop would)
-    float part[kApanMaxK];
+    const int first = ((__builtin_amdgcn_readfirstlane(a.mb_head[v]) - cnt) % K + K) % K;
+    auto slot = [&](int j) { return first + j < K ? first + j : first + j - K; };
+    const float *box = a.mb + (int64_t)v * K * D_m;
+    float x[NC][CD], u[CD];
 #pragma unroll
-    for (int j = 0; j < kApanMaxK; ++j)
+    for (int j = 0; j < NC; ++j) {
+        const float *row = box + (int64_t)slot(min(j, cnt - 1)) * D_m;
+#pragma unroll
+        for (int i = 0; i < CD; ++i)
+            x[j][i] = row[min(lane + kWave * i, D_m - 1)];
+    }
+    const double tj = a.mb_ts[(int64_t)v * K + slot(min(lane, cnt - 1))];
+    const float *up = a.u + (int64_t)p * D_x;
+#pragma unroll
+    for (int i = 0; i < CD; ++i)
+        u[i] = up[min(lane + kWave * i, D_m - 1)];
+    const double mts = a.mem_ts[v];
+    issue_fence();
+    if (lane < cnt)
+        a.f_mb_ts[(int64_t)p * K + lane] = tj;
+    const long long tb = __double_as_longlong(tj);
+    const int tlo = (int)tb, thi = (int)(tb >> 32);
+    auto time_of = [&](int j) {
+        const unsigned l = (unsigned)__builtin_amdgcn_readlane(tlo, j);
+        const long long h = __builtin_amdgcn_readlane(thi, j);
+        return __longlong_as_double((h << 32) | l);
+    };
+    const double tref = time_of(cnt - 1);
+    float part[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
         part[j] = 0.f;
-    for (int k = lane; k < D_m; k += kWave) {
-        const float uk = u[k];
-#pragma unroll
-        for (int j = 0; j < kApanMaxK; ++j)
-            if (j < cnt)
-                part[j] += uk * rows[(int64_t)j * D_m + k];
-    }
-    for (int d = lane; d < D_t; d += kWave) {
-        const float ud = u[D_m + d];
+    for (int d = lane; d < D_t; d += kWave) {   // while the rows are on their way
+        const float ud = up[D_m + d];
         const double om = a.omega[d], be = a.beta[d];
+        a.X[(int64_t)p * D_x + D_m + d] = time_enc(om, be, tref - mts);
 #pragma unroll
-        for (int j = 0; j < kApanMaxK; ++j)
+        for (int j = 0; j < NC; ++j)
             if (j < cnt)
-                part[j] += ud * time_enc(om, be, tref - ts[j]);
+                part[j] = fmaf(ud, time_enc(om, be, tref - time_of(j)), part[j]);
     }
-    const float qb = a.qb[p];
+#pragma unroll
+    for (int i = 0; i < CD; ++i)
+        u[i] = lane + kWave * i < D_m ? u[i] : 0.f;
     float mine = -INFINITY;   // lane j < cnt: the score of mail j
 #pragma unroll
-    for (int j = 0; j < kApanMaxK; ++j)
+    for (int j = 0; j < NC; ++j)
         if (j < cnt) {
-            const float sc = (wave_sum(part[j]) + qb) * a.scale;
-            if (lane == j)
-                mine = sc;
+            float *row = a.f_mb + ((int64_t)p * K + j) * D_m;
+#pragma unroll
+            for (int i = 0; i < CD; ++i) {
+                part[j] = fmaf(u[i], x[j][i], part[j]);
+                if (lane + kWave * i < D_m)
+                    row[lane + kWave * i] = x[j][i];
+            }
+            const float sc = wave_total(part[j]) * a.scale;
+            mine = lane == j ? sc : mine;
         }
     float mx = mine;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
         mx = fmaxf(mx, __shfl_xor(mx, o, kWave));
     const float ex = lane < cnt ? expf(mine - mx) : 0.f;
-    const float al = ex / wave_sum(ex);
-    float alv[kApanMaxK];   // every lane holds every weight (shuffles in uniform flow)
+    const float al = ex / wave_total(ex);
+    float acc[CD];
 #pragma unroll
-    for (int j = 0; j < kApanMaxK; ++j)
-        alv[j] = __shfl(al, j < cnt ? j : 0, kWave);
-    for (int k = lane; k < D_m; k += kWave) {
-        float acc = 0.f;
+    for (int i = 0; i < CD; ++i)
+        acc[i] = 0.f;
 #pragma unroll
-        for (int j = 0; j < kApanMaxK; ++j)
-            if (j < cnt)
-                acc += alv[j] * rows[(int64_t)j * D_m + k];
-        x[k] = acc;
-    }
-    for (int d = lane; d < D_t; d += kWave)
-        x[D_m + d] = time_enc(a.omega[d], a.beta[d], tref - a.f_mem_ts[p]);
-    if (lane == 0)
+    for (int j = 0; j < NC; ++j)
+        if (j < cnt) {
+            const float w = lane_value(al, j);
+#pragma unroll
+            for (int i = 0; i < CD; ++i)
+                acc[i] = fmaf(w, x[j][i], acc[i]);
+        }
+#pragma unroll
+    for (int i = 0; i < CD; ++i)
+        if (lane + kWave * i < D_m)
+            a.X[(int64_t)p * D_x + lane + kWave * i] = acc[i];
+    if (lane == 0) {
         a.t_new[p] = tref;
+        if (a.new_ts)
+            a.new_ts[p] = tref;
+    }
 }
 
-// q . b_k per node (the common part of every score), one wavefront per node
-__global__ __launch_bounds__(256) void k_apan_qb(const int32_t *__restrict__ n_nodes, int cap,
-                                                 int M, const float *__restrict__ Q,
-                                                 const float *__restrict__ b_k,
-                                                 float *__restrict__ qb)
+// The query projection's constant part W_q phi(0) + b_q, one wavefront per unit
+__global__ __launch_bounds__(256) void k_apan_cq(int M, int D_t, const float *__restrict__ W_q,
+                                                 const float *__restrict__ b_q,
+                                                 const double *__restrict__ beta,
+                                                 double *__restrict__ cq)
 {
-    const int p = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    if (p >= min(*n_nodes, cap))
+    const int d = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6), lane = threadIdx.x & 63;
+    if (d >= M)
         return;
-    float acc = 0.f;
-    for (int k = lane; k < M; k += kWave)
-        acc += Q[(int64_t)p * M + k] * b_k[k];
-    acc = wave_sum(acc);
+    double acc = 0.0;
+    for (int t = lane; t < D_t; t += kWave)
+        acc += (double)W_q[(int64_t)d * (M + D_t) + M + t] * cos(beta[t]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        acc += __shfl_xor(acc, o, kWave);
     if (lane == 0)
-        qb[p] = acc;
+        cq[d] = acc + (double)b_q[d];
+}
+
+// The key projection with the query's folded in, in fp64 at creation:
+// u = W_k^t (W_q [s || phi(0)] + b_q) = Wqk^t s + c_u, Wqk [M x D_x].
+__global__ __launch_bounds__(256) void k_apan_fold(int M, int D_x, int D_t,
+                                                   const float *__restrict__ W_q,
+                                                   const double *__restrict__ cq,
+                                                   const float *__restrict__ W_k,
+                                                   float *__restrict__ Wqk,
+                                                   float *__restrict__ c_u)
+{
+    const int x = blockIdx.x * blockDim.x + threadIdx.x, m = blockIdx.y;
+    if (x >= D_x)
+        return;
+    double acc = 0.0;
+    for (int d = 0; d < M; ++d)
+        acc += (m < M ? (double)W_q[(int64_t)d * (M + D_t) + m] : cq[d]) *
+               (double)W_k[(int64_t)d * D_x + x];
+    if (m < M)
+        Wqk[(int64_t)m * D_x + x] = (float)acc;
+    else
+        c_u[x] = (float)acc;
 }
 
 // The GRU cell from the gate pre-activations Gx = X W_ih^t + b_ih and
@@ -227,55 +259,65 @@ __global__ __launch_bounds__(256) void k_apan_gru(const int32_t *__restrict__ n_
     s_new[(int64_t)p * M + j] = (1.f - z) * n + z * h;
 }
 
-// h[r] = s_new[root_pos[r]] (the embedding is the updated memory)
-__global__ __launch_bounds__(256) void k_apan_embed(int R, int M,
-                                                    const int32_t *__restrict__ root_pos,
-                                                    const float *__restrict__ s_new,
-                                                    float *__restrict__ h)
-{
-    const int r = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
-    if (r >= R)
-        return;
-    wave_copy_row(h + (int64_t)r * M, s_new + (int64_t)root_pos[r] * M, M, threadIdx.x & 63);
-}
-
-// ------------------------------------------------------------- staging
-// Delivery d = ((k 2 + role)(nb + 1) + slot) of batch event k: the mail of
+// What follows the new memories, one launch: the sort keys of the deliveries
+// (first, they take longest), the embeddings h[r] = s_new[root_pos[r]], and
+// the staged memory rows of the batch's endpoints.
+//   Delivery d = ((k 2 + role)(nb + 1) + slot) of batch event k: the mail of
 // endpoint v (role 0: src, 1: dst) to v (slot 0) or to its neighbour in
 // sampled slot (slot - 1) of root role b + k.  Sort key: the node, or N (past
 // every node) for empty and unused deliveries.
-__global__ __launch_bounds__(256) void k_apan_keys(int32_t b, int nb, int propagate, int32_t N,
-                                                   const int32_t *__restrict__ root,
-                                                   const int32_t *__restrict__ nbr,
-                                                   const int32_t *__restrict__ cnt, SortPlan p)
+//   Memory rows by node-set position: flag[p] = 1 and the new memory for every
+// position that is a source or destination, one wavefront per endpoint
+// occurrence (all occurrences of a node write the same values).
+struct AfterArgs {
+    int32_t b, nb, propagate, N, M;
+    int n_keys, n_embed;   // workgroups of the first two parts
+    const int32_t *root, *nbr, *cnt, *root_pos, *nodes;
+    const float *s_new;
+    const double *t_new;
+    float *h;
+    int32_t *flag, *node;
+    float *r_mem;
+    double *r_ts;
+    SortPlan sort;
+};
+
+__global__ __launch_bounds__(256) void k_apan_after(AfterArgs a)
 {
     __shared__ int32_t count[1 << kSortDigit];
-    const int per = nb + 1;
-    sort_keys_tile(p, blockIdx.x, count, [&](int64_t d) {
-        const int slot = (int)(d % per), kr = (int)(d / per), role = kr & 1, k = kr >> 1;
-        const int r = role * b + k;
-        int32_t w = N;
-        if (slot == 0)
-            w = root[r];
-        else if (propagate && slot - 1 < cnt[r])
-            w = nbr[(int64_t)r * nb + slot - 1];
-        return min((uint32_t)w, (uint32_t)N);
-    });
-}
-
-// Segment bounds by node id over the sorted keys
-__global__ __launch_bounds__(256) void k_apan_bounds(int64_t n, const uint32_t *__restrict__ keys,
-                                                     int32_t N, int32_t *__restrict__ seg,
-                                                     int32_t *__restrict__ seg_end)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n || keys[i] >= (uint32_t)N)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, M = a.M;
+    int blk = blockIdx.x;
+    if (blk < a.n_keys) {
+        const int per = a.nb + 1;
+        sort_keys_tile(a.sort, blk, count, [&](int64_t d) {
+            const int slot = (int)(d % per), kr = (int)(d / per), role = kr & 1, k = kr >> 1;
+            const int r = role * a.b + k;
+            int32_t w = a.N;
+            if (slot == 0)
+                w = a.root[r];
+            else if (a.propagate && slot - 1 < a.cnt[r])
+                w = a.nbr[(int64_t)r * a.nb + slot - 1];
+            return min((uint32_t)w, (uint32_t)a.N);
+        });
         return;
-    const uint32_t w = keys[i];
-    if (i == 0 || keys[i - 1] != w)
-        seg[w] = (int32_t)i;
-    if (i == n - 1 || keys[i + 1] != w)
-        seg_end[w] = (int32_t)(i + 1);
+    }
+    blk -= a.n_keys;
+    if (blk < a.n_embed) {
+        const int r = blk * 4 + wave;
+        if (r < 3 * a.b)
+            wave_copy_row(a.h + (int64_t)r * M, a.s_new + (int64_t)a.root_pos[r] * M, M, lane);
+        return;
+    }
+    const int e = (blk - a.n_embed) * 4 + wave;
+    if (e >= 2 * a.b)
+        return;
+    const int p = a.root_pos[e];
+    wave_copy_row(a.r_mem + (int64_t)p * M, a.s_new + (int64_t)p * M, M, lane);
+    if (lane == 0) {
+        a.flag[p] = 1;
+        a.node[p] = a.nodes[p];
+        a.r_ts[p] = a.t_new[p];
+    }
 }
 
 struct StageArgs2 {
@@ -283,7 +325,6 @@ struct StageArgs2 {
     int64_t first;
     const uint32_t *keys;       // sorted
     const int32_t *dels;        // their deliveries
-    const int32_t *seg, *seg_end;
     const int32_t *root_pos;    // [3b]
     const float *s_new, *efeat;
     const double *t;
@@ -295,25 +336,28 @@ struct StageArgs2 {
 
 // One wavefront per sorted delivery: rows that the node's mailbox keeps (the
 // last K of its segment) are written with their rank among the kept ones.
+// Lane l looks at the key K - l places before (l <= K) or l - K after, which
+// is as far as a kept row's segment matters (K <= 16).
 __global__ __launch_bounds__(256) void k_apan_stage_mail(StageArgs2 a, int64_t n)
 {
     const int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, K = a.K;
     if (i >= n)
         return;
-    if (a.keys[i] >= (uint32_t)a.N) {
+    const uint32_t w = a.keys[i];
+    const int64_t at = i - K + lane;
+    const bool same = lane <= 2 * K && at >= 0 && at < n &&
+                      a.keys[min(max(at, (int64_t)0), n - 1)] == w;
+    // the segment is contiguous: its rows before and after this one, up to K
+    const uint64_t near = __ballot(same);
+    const int before = __popcll(near & ((uint64_t(1) << K) - 1));
+    const int after = __popcll(near >> (K + 1));
+    if (w >= (uint32_t)a.N || after >= K) {
         if (lane == 0)
             a.d_keep[i] = 0;
         return;
     }
-    const int32_t w = (int32_t)a.keys[i];
-    const int64_t lo = a.seg[w], hi = a.seg_end[w];
-    const int64_t keep_from = max(lo, hi - a.K);
-    if (i < keep_from) {
-        if (lane == 0)
-            a.d_keep[i] = 0;
-        return;
-    }
+    const int keep = min(before + 1 + after, K), rank = keep - 1 - after;
     const int d = a.dels[i];
     const int per = a.nb + 1;
     const int kr = d / per, role = kr & 1, k = kr >> 1;
@@ -325,37 +369,10 @@ __global__ __launch_bounds__(256) void k_apan_stage_mail(StageArgs2 a, int64_t n
     if (D_e > 0)
         wave_copy_row(row + 2 * M, a.efeat + (a.first + k) * D_e, D_e, lane);
     if (lane == 0) {
-        a.d_node[i] = w;
-        a.d_rank[i] = (int32_t)(i - keep_from);
-        a.d_keep[i] = (int32_t)(hi - keep_from);
+        a.d_node[i] = (int32_t)w;
+        a.d_rank[i] = rank;
+        a.d_keep[i] = keep;
         a.d_t[i] = a.t[a.first + k];
-    }
-}
-
-// Memory rows of the batch's endpoints, by node-set position: flag[p] = 1 and
-// the new memory for every position that is a source or destination.
-__global__ __launch_bounds__(256) void k_apan_stage_mem(int32_t b, int M,
-                                                        const int32_t *__restrict__ root_pos,
-                                                        const int32_t *__restrict__ nodes,
-                                                        const float *__restrict__ s_new,
-                                                        const double *__restrict__ new_ts,
-                                                        int32_t *__restrict__ flag,
-                                                        int32_t *__restrict__ node,
-                                                        float *__restrict__ r_mem,
-                                                        double *__restrict__ r_ts)
-{
-    // one wavefront per endpoint occurrence; all occurrences of a node write
-    // the same values (plain stores)
-    const int e = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    if (e >= 2 * b)
-        return;
-    const int p = root_pos[e];
-    wave_copy_row(r_mem + (int64_t)p * M, s_new + (int64_t)p * M, M, lane);
-    if (lane == 0) {
-        flag[p] = 1;
-        node[p] = nodes[p];
-        r_ts[p] = new_ts[p];
     }
 }
 
@@ -367,47 +384,42 @@ __global__ __launch_bounds__(256) void k_apan_clear_flags(int32_t *__restrict__ 
 }
 
 // ------------------------------------------------------------- commit
-__global__ __launch_bounds__(256) void k_apan_commit_mem(int cap, int M, int64_t iter,
-                                                         const int32_t *__restrict__ flag,
-                                                         const int32_t *__restrict__ node,
-                                                         const float *__restrict__ r_mem,
-                                                         const double *__restrict__ r_ts,
-                                                         float *__restrict__ mem,
-                                                         double *__restrict__ mem_ts,
-                                                         int32_t *__restrict__ ver)
-{
-    const int p = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    if (p >= cap || !flag[p])
-        return;
-    const int v = node[p];
-    wave_copy_row(mem + (int64_t)v * M, r_mem + (int64_t)p * M, M, lane);
-    if (lane == 0) {
-        mem_ts[v] = r_ts[p];
-        ver[v] = (int32_t)iter;
-    }
-}
+// One write set's memory rows (by node-set position, one wavefront each), and
+// its kept mails into the ring at head + rank (heads are updated after)
+struct CommitArgs {
+    int cap, n_mem, M, D_m, K;   // n_mem: workgroups of the memory rows
+    int64_t iter, n_del;
+    const int32_t *flag, *node, *d_node, *d_rank, *d_keep, *head;
+    const float *r_mem, *d_mail;
+    const double *r_ts, *d_t;
+    float *mem, *mb;
+    double *mem_ts, *mb_ts;
+    int32_t *ver;
+};
 
-// kept mails into the ring at head + rank (heads are updated after)
-__global__ __launch_bounds__(256) void k_apan_commit_mail(int64_t n, int D_m, int K,
-                                                          const int32_t *__restrict__ d_node,
-                                                          const int32_t *__restrict__ d_rank,
-                                                          const int32_t *__restrict__ d_keep,
-                                                          const float *__restrict__ d_mail,
-                                                          const double *__restrict__ d_t,
-                                                          const int32_t *__restrict__ head,
-                                                          float *__restrict__ mb,
-                                                          double *__restrict__ mb_ts)
+__global__ __launch_bounds__(256) void k_apan_commit(CommitArgs a)
 {
-    const int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (i >= n || d_keep[i] == 0)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if ((int)blockIdx.x < a.n_mem) {
+        const int p = (int)blockIdx.x * 4 + wave;
+        if (p >= a.cap || !a.flag[p])
+            return;
+        const int v = a.node[p];
+        wave_copy_row(a.mem + (int64_t)v * a.M, a.r_mem + (int64_t)p * a.M, a.M, lane);
+        if (lane == 0) {
+            a.mem_ts[v] = a.r_ts[p];
+            a.ver[v] = (int32_t)a.iter;
+        }
         return;
-    const int v = d_node[i];
-    const int slot = (head[v] + d_rank[i]) % K;
-    wave_copy_row(mb + ((int64_t)v * K + slot) * D_m, d_mail + i * D_m, D_m, lane);
+    }
+    const int64_t i = ((int64_t)blockIdx.x - a.n_mem) * 4 + wave;
+    if (i >= a.n_del || a.d_keep[i] == 0)
+        return;
+    const int v = a.d_node[i];
+    const int slot = (a.head[v] + a.d_rank[i]) % a.K;
+    wave_copy_row(a.mb + ((int64_t)v * a.K + slot) * a.D_m, a.d_mail + i * a.D_m, a.D_m, lane);
     if (lane == 0)
-        mb_ts[(int64_t)v * K + slot] = d_t[i];
+        a.mb_ts[(int64_t)v * a.K + slot] = a.d_t[i];
 }
 
 __global__ __launch_bounds__(256) void k_apan_commit_heads(int64_t n, int K,
@@ -513,19 +525,19 @@ struct tgm_apan {
     // weights (plain, device)
     float *W_ih = nullptr, *W_hh = nullptr, *b_ih = nullptr, *b_hh = nullptr;
     float *W_q = nullptr, *b_q = nullptr, *W_k = nullptr, *b_k = nullptr;
-    double *omega = nullptr, *beta = nullptr;
+    double *omega = nullptr, *beta = nullptr, *cq = nullptr;   // cq: W_q phi(0) + b_q
     // committed tables
     float *mem = nullptr, *mb = nullptr;
     double *mem_ts = nullptr, *mb_ts = nullptr;
     int32_t *ver = nullptr, *head = nullptr, *cnt = nullptr;
     // fetched rows of the last step and the updater's work space
-    float *f_mem = nullptr, *f_mb = nullptr, *Xq = nullptr, *Q = nullptr, *U = nullptr,
-          *qb = nullptr, *X = nullptr, *Gx = nullptr, *Gh = nullptr;
+    float *Wqk = nullptr, *c_u = nullptr;   // the key projection with the query's folded in
+    float *f_mem = nullptr, *f_mb = nullptr, *U = nullptr, *X = nullptr, *Gx = nullptr,
+          *Gh = nullptr;
     double *f_mem_ts = nullptr, *f_mb_ts = nullptr, *t_new = nullptr;
     int32_t *f_ver = nullptr, *f_cnt = nullptr;
-    // staging: keys, sort, segments
+    // staging
     SortBuffers sort;   // deliveries by node
-    int32_t *seg = nullptr, *seg_end = nullptr;
     // ring of s + 1 write sets: memory rows by node-set position, mail rows
     // by sorted delivery position
     struct Slot {
@@ -555,18 +567,17 @@ tgm_status_t apan_commit_through(tgm_apan *a, int64_t target, hipStream_t s)
             return TGM_EORDER;
         const int64_t r = j % slots;
         const int64_t cap = a->max_nodes, md = a->max_del();
-        TGM_LAUNCH(k_apan_commit_mem, dim3((unsigned)cdiv(cap * kWave, 256)), dim3(256), 0, s,
-                   (int)cap, a->M, j, a->r_flag + r * cap, a->r_node + r * cap,
-                   a->r_mem + r * cap * a->M, a->r_ts + r * cap, a->mem, a->mem_ts, a->ver);
-        if (sl.n_del > 0) {
-            TGM_LAUNCH(k_apan_commit_mail, dim3((unsigned)cdiv(sl.n_del * kWave, 256)),
-                       dim3(256), 0, s, sl.n_del, a->D_m, a->K, a->d_node + r * md,
-                       a->d_rank + r * md, a->d_keep + r * md, a->d_mail + r * md * a->D_m,
-                       a->d_t + r * md, a->head, a->mb, a->mb_ts);
+        CommitArgs ca{(int)cap, (int)cdiv(cap, 4), a->M, a->D_m, a->K, j, sl.n_del,
+                      a->r_flag + r * cap, a->r_node + r * cap, a->d_node + r * md,
+                      a->d_rank + r * md, a->d_keep + r * md, a->head, a->r_mem + r * cap * a->M,
+                      a->d_mail + r * md * a->D_m, a->r_ts + r * cap, a->d_t + r * md, a->mem,
+                      a->mb, a->mem_ts, a->mb_ts, a->ver};
+        TGM_LAUNCH(k_apan_commit, dim3((unsigned)(ca.n_mem + cdiv(sl.n_del, 4))), dim3(256), 0, s,
+                   ca);
+        if (sl.n_del > 0)
             TGM_LAUNCH(k_apan_commit_heads, dim3((unsigned)cdiv(sl.n_del, 256)), dim3(256), 0,
                        s, sl.n_del, a->K, a->d_node + r * md, a->d_rank + r * md,
                        a->d_keep + r * md, a->head, a->cnt);
-        }
         sl.staged = false;
         a->committed_through = j;
     }
@@ -583,9 +594,8 @@ extern "C" tgm_status_t tgm_apan_destroy(tgm_apan_t a)
         return TGM_EINVAL;
     void *bufs[] = {a->W_ih, a->W_hh, a->b_ih, a->b_hh, a->W_q, a->b_q, a->W_k, a->b_k,
                     a->omega, a->beta, a->mem, a->mb, a->mem_ts, a->mb_ts, a->ver, a->head,
-                    a->cnt, a->f_mem, a->f_mb, a->Xq, a->Q, a->U, a->qb, a->X, a->Gx, a->Gh,
-                    a->f_mem_ts, a->f_mb_ts, a->t_new, a->f_ver, a->f_cnt, a->seg,
-                    a->seg_end, a->r_flag, a->r_node,
+                    a->cnt, a->Wqk, a->c_u, a->cq, a->f_mem, a->f_mb, a->U, a->X, a->Gx, a->Gh,
+                    a->f_mem_ts, a->f_mb_ts, a->t_new, a->f_ver, a->f_cnt, a->r_flag, a->r_node,
                     a->r_mem, a->r_ts, a->d_node, a->d_rank, a->d_keep, a->d_mail, a->d_t};
     for (void *b : bufs)
         (void)hipFree(b);
@@ -648,10 +658,10 @@ extern "C" tgm_status_t tgm_apan_create(const tgm_apan_desc *d, const tgm_weight
     alloc(&a->cnt, N);
     alloc(&a->f_mem, C * M);
     alloc(&a->f_mb, C * K * D_m);
-    alloc(&a->Xq, C * (M + D_t));
-    alloc(&a->Q, C * M);
+    alloc(&a->Wqk, M * D_x);
+    alloc(&a->c_u, D_x);
+    alloc(&a->cq, M);
     alloc(&a->U, C * D_x);
-    alloc(&a->qb, C);
     alloc(&a->X, C * D_x);
     alloc(&a->Gx, C * 3 * M);
     alloc(&a->Gh, C * 3 * M);
@@ -660,8 +670,6 @@ extern "C" tgm_status_t tgm_apan_create(const tgm_apan_desc *d, const tgm_weight
     alloc(&a->t_new, C);
     alloc(&a->f_ver, C);
     alloc(&a->f_cnt, C);
-    alloc(&a->seg, N);
-    alloc(&a->seg_end, N);
     alloc(&a->r_flag, slots * C);
     alloc(&a->r_node, slots * C);
     alloc(&a->r_mem, slots * C * M);
@@ -696,6 +704,10 @@ extern "C" tgm_status_t tgm_apan_create(const tgm_apan_desc *d, const tgm_weight
                            a->mem, a->mem_ts, a->ver, a->mb, a->mb_ts, a->head, a->cnt);
         hipLaunchKernelGGL(k_apan_clear_flags, dim3((unsigned)cdiv(slots * C, 256)), dim3(256), 0,
                            s, a->r_flag, (int)(slots * C));
+        hipLaunchKernelGGL(k_apan_cq, dim3((unsigned)cdiv(M, 4)), dim3(256), 0, s, a->M, a->D_t,
+                           a->W_q, a->b_q, a->beta, a->cq);
+        hipLaunchKernelGGL(k_apan_fold, dim3((unsigned)cdiv(D_x, 256), (unsigned)M + 1), dim3(256),
+                           0, s, a->M, a->D_x, a->D_t, a->W_q, a->cq, a->W_k, a->Wqk, a->c_u);
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
             st = TGM_EDEVICE;
     }
@@ -730,18 +742,18 @@ extern "C" tgm_status_t tgm_apan_step(tgm_apan_t a, tgm_graph_t g, int64_t iter,
     hipStream_t s = as_stream(stream);
     // the write sets a fetch at iter sees: <= iter - 1 - s (Eq. 2)
     TGM_TRY_STATUS(apan_commit_through(a, iter - 1 - a->s, s));
+    const int slots = a->s + 1;
+    tgm_apan::Slot &sl = a->ring[iter % slots];
+    if (sl.staged)
+        return TGM_EORDER;   // cannot happen: commits run ahead of the ring
+    const int64_t r = iter % slots, C = a->max_nodes, MD = a->max_del();
     ApanRows ar{sb->nodes, sb->n_nodes, cap, M, D_m, D_t, K, a->mem, a->mb, a->mem_ts,
                 a->mb_ts, a->ver, a->head, a->cnt, a->f_mem, a->f_mb, a->f_mem_ts,
-                a->f_mb_ts, a->f_ver, a->f_cnt};
+                a->f_mb_ts, a->f_ver, a->f_cnt, a->r_flag + r * C, (int)C, (int)cdiv(cap, 4),
+                a->U, a->omega, a->beta, 1.f / sqrtf((float)M), a->X, a->t_new, new_mem_ts};
+    TGM_LAUNCH(k_apan_gather, dim3((unsigned)(ar.n_gather + cdiv(C, 256))), dim3(256), 0, s, ar);
     if (cap > 0) {
-        TGM_LAUNCH(k_apan_gather, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)), dim3(256), 0,
-                   s, ar);
-        // the mailbox attention: q, u = q W_k, q . b_k, then scores and the
-        // aggregate per node
-        TGM_LAUNCH(k_apan_query_rows, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)),
-                   dim3(256), 0, s, sb->n_nodes, cap, M, D_t, a->f_mem, a->omega, a->beta,
-                   a->Xq);
-        auto mul = [&](bool tb, int n, int k, const float *x, const float *w, int ldw, float *out,
+        auto mul = [&](int n, int k, const float *x, const float *w, int ldw, float *out,
                        const float *bias) {   // rows of the node set only
             GemmProb p;
             p.m = cap;
@@ -755,51 +767,36 @@ extern "C" tgm_status_t tgm_apan_step(tgm_apan_t a, tgm_graph_t g, int64_t iter,
             p.ldc = n;
             p.bias = bias;
             p.live = sb->n_nodes;
-            return gemm_launch(false, tb, &p, 1, s);
+            return p;
         };
-        TGM_TRY_STATUS(mul(true, M, M + D_t, a->Xq, a->W_q, M + D_t, a->Q, a->b_q));
-        TGM_TRY_STATUS(mul(false, D_x, M, a->Q, a->W_k, D_x, a->U, nullptr));
-        TGM_LAUNCH(k_apan_qb, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)), dim3(256), 0, s,
-                   sb->n_nodes, cap, M, a->Q, a->b_k, a->qb);
-        AttnArgs2 aa{sb->n_nodes, cap, M, D_m, D_t, K, 1.f / sqrtf((float)M), a->U, a->qb,
-                     a->f_mb, a->f_mb_ts, a->f_mem_ts, a->omega, a->beta, a->f_cnt, a->X,
-                     a->t_new};
-        TGM_LAUNCH(k_apan_attn, dim3((unsigned)cdiv((int64_t)cap * kWave, 256)), dim3(256), 0, s,
-                   aa);
+        // the mailbox attention: u per node, then scores and the aggregate
+        const GemmProb u = mul(D_x, M, a->f_mem, a->Wqk, D_x, a->U, a->c_u);
+        TGM_TRY_STATUS(gemm_launch(false, false, &u, 1, s));
+        const dim3 grid((unsigned)cdiv((int64_t)cap * kWave, 256));
+        if (K <= 10 && D_m <= 6 * kWave)   // 60 registers of mails, else 128
+            TGM_LAUNCH((k_apan_attn<10, 6>), grid, dim3(256), 0, s, ar);
+        else
+            TGM_LAUNCH((k_apan_attn<kApanMaxK, 8>), grid, dim3(256), 0, s, ar);
         // the GRU on [aggregate || phi(t_newest - mem_ts)]
-        TGM_TRY_STATUS(mul(true, 3 * M, D_x, a->X, a->W_ih, D_x, a->Gx, a->b_ih));
-        TGM_TRY_STATUS(mul(true, 3 * M, M, a->f_mem, a->W_hh, M, a->Gh, a->b_hh));
+        const GemmProb g[2] = {mul(3 * M, D_x, a->X, a->W_ih, D_x, a->Gx, a->b_ih),
+                               mul(3 * M, M, a->f_mem, a->W_hh, M, a->Gh, a->b_hh)};
+        TGM_TRY_STATUS(gemm_launch(false, true, g, 2, s));
         TGM_LAUNCH(k_apan_gru, dim3((unsigned)cdiv((int64_t)cap * M, 256)), dim3(256), 0, s,
                    sb->n_nodes, cap, M, a->f_cnt, a->Gx, a->Gh, a->f_mem, mem_new);
-        if (new_mem_ts)
-            TGM_HIP(hipMemcpyAsync(new_mem_ts, a->t_new, sizeof(double) * cap,
-                                   hipMemcpyDeviceToDevice, s));
     }
-    if (R > 0)
-        TGM_LAUNCH(k_apan_embed, dim3((unsigned)cdiv((int64_t)R * kWave, 256)), dim3(256), 0, s,
-                   R, M, sb->root_pos, mem_new, h);
-    // the write set of iter: memory rows of the endpoints, mail deliveries
-    const int slots = a->s + 1;
-    tgm_apan::Slot &sl = a->ring[iter % slots];
-    if (sl.staged)
-        return TGM_EORDER;   // cannot happen: commits run ahead of the ring
-    const int64_t r = iter % slots, C = a->max_nodes, MD = a->max_del();
-    TGM_LAUNCH(k_apan_clear_flags, dim3((unsigned)cdiv(C, 256)), dim3(256), 0, s,
-               a->r_flag + r * C, (int)C);
-    if (b > 0)
-        TGM_LAUNCH(k_apan_stage_mem, dim3((unsigned)cdiv((int64_t)2 * b * kWave, 256)),
-                   dim3(256), 0, s, b, M, sb->root_pos, sb->nodes, mem_new, a->t_new,
-                   a->r_flag + r * C, a->r_node + r * C, a->r_mem + r * C * M, a->r_ts + r * C);
+    // the embeddings and the write set of iter: memory rows of the endpoints,
+    // mail deliveries
     const int64_t n_del = (int64_t)2 * b * (nb + 1);
-    if (n_del > 0) {
+    if (b > 0) {
         const SortPlan plan = sort_plan(a->sort, n_del);
-        TGM_LAUNCH(k_apan_keys, dim3((unsigned)sort_tiles(n_del)), dim3(256), 0, s, b, nb,
-                   a->propagate, a->N, sb->root, sb->nbr, sb->cnt, plan);
+        AfterArgs fa{b, nb, a->propagate, a->N, M, (int)sort_tiles(n_del), (int)cdiv(R, 4),
+                     sb->root, sb->nbr, sb->cnt, sb->root_pos, sb->nodes, mem_new, a->t_new, h,
+                     a->r_flag + r * C, a->r_node + r * C, a->r_mem + r * C * M, a->r_ts + r * C,
+                     plan};
+        TGM_LAUNCH(k_apan_after, dim3((unsigned)(fa.n_keys + fa.n_embed + cdiv(2 * b, 4))),
+                   dim3(256), 0, s, fa);
         TGM_TRY_STATUS(sort_launch(a->sort, plan, s));
-        TGM_LAUNCH(k_apan_bounds, dim3((unsigned)cdiv(n_del, 256)), dim3(256), 0, s, n_del,
-                   a->sort.out_keys, a->N, a->seg, a->seg_end);
-        StageArgs2 sa{b, nb, M, a->D_e, D_m, K, a->N, lo, a->sort.out_keys, a->sort.out_vals, a->seg,
-                      a->seg_end,
+        StageArgs2 sa{b, nb, M, a->D_e, D_m, K, a->N, lo, a->sort.out_keys, a->sort.out_vals,
                       sb->root_pos, mem_new, g->efeat, g->t, a->d_node + r * MD,
                       a->d_rank + r * MD, a->d_keep + r * MD, a->d_mail + r * MD * D_m,
                       a->d_t + r * MD};
