@@ -127,11 +127,13 @@ extern "C" tgm_status_t tgm_stage_run(tgm_graph_t g, tgm_state_t st, tgm_model_t
                 else
                     next_ready = ev[(c + 1) & 1];
             }
+            // the winners are the run's last outputs: every iteration's would be
+            // overwritten by the next one's (a launch of 4 us each)
             // in training mode the next fetch waits for the training step,
             // which reads this iteration's fetch buffers
             const tgm_sample_buffers *next = more ? &sb[(k + 1) % nsb] : nullptr;
             TGM_TRY_STATUS(compute_iteration(st, m, g, i0 + k, sb[k % nsb], *fb, cap, lo, b, nb,
-                                             mem_new, new_mem_ts, winner, h,
+                                             mem_new, new_mem_ts, more ? nullptr : winner, h,
                                              train ? nullptr : next, (int32_t)(1 + k % nsb),
                                              xwin[k % nsb], xtag[k % nsb], main, inplace(k),
                                              inplace(k + 1), next_ready));
