@@ -2386,6 +2386,13 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
         for (int dc = 0; dc < kAggDC; ++dc)
             sa[dc] = *reinterpret_cast<const f4 *>(krow + min(16 * dc + q4, M - 4));
     }
+    float sr_[2];   // s'_r, stored below: [sum alpha seedV || s'_r || 0]
+    {
+        const float *srow = g.mem_new + (int64_t)(pv_ok ? pv : 0) * M;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            sr_[u] = srow[min(lane + kWave * u, M - 1)];
+    }
     issue_fence();
     if (seeds) {
         f4 acc = f4{0, 0, 0, 0};
@@ -2399,16 +2406,29 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
                 Sk[srow * H + ce] = acc[v];
         }
     }
+    if (own) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (lane + kWave * u < M)
+                AO[wave * SAO + M + lane + kWave * u] = pv_ok ? sr_[u] : 0.f;
+        for (int k = 2 * M + lane; k < OC * 16; k += kWave)
+            AO[wave * SAO + k] = 0.f;
+    }
     // 1e. the own root's slot rows: edge features (HBM), then the time codes
     // phi(t_root - t_slot) computed while those are in flight.  Every load is
     // unconditional, at clamped columns and events: with a condition per
     // element (200 of them) and a reduction per score a wavefront issued 3,100
     // vector instructions instead of 1,900 (113.5 against 110 us for 12,000
     // roots with the node projections, 19.4 against 16.6 us for 600 small
-    // ones; touching the rows' lines earlier gained nothing).
+    // ones; touching the rows' lines earlier gained nothing).  The registers
+    // are all taken here and in the scores (128, four waves per SIMD): with
+    // s'_r, cn, q4 and the event ids held through both, six were spilled, 15 MB
+    // written and read back per 12,000 roots (109.6 against 104.2 us).
     constexpr int CT = kAggTCols, CX = CE + CT;
     float xs[NBM][CX];   // slot j's edge features lane + 64 i, then its time codes
     const int cu = __builtin_amdgcn_readfirstlane(c);
+    // filled slots whose event id is out of range: no edge features
+    const uint64_t no_edge = __ballot(lane < cu && my_e < 0);
     if (D_e > 0) {
 #pragma unroll
         for (int j = 0; j < NBM; ++j) {
@@ -2447,22 +2467,21 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
             }
         }
     }
-    // a filled slot whose event id is out of range has no edge features
-    if (D_e > 0 && __ballot(lane < cu && my_e < 0) != 0)
+    if (D_e > 0 && no_edge != 0)
 #pragma unroll
         for (int j = 0; j < NBM; ++j)
-            if (__builtin_amdgcn_readlane(my_e, j) < 0)
+            if ((no_edge >> j) & 1)
 #pragma unroll
                 for (int i = 0; i < CE; ++i)
                     xs[j][i] = 0.f;
     __syncthreads();
 
     // 2. scores, softmax, aggregates (own root), two heads at a time; the value
-    // seeds of the lane's columns d = lane, lane + 64 and s'_r load first
+    // seeds of the lane's columns d = lane, lane + 64 load first
     const float scale = 1.0f / sqrtf((float)d_h);
     f4 ring[kAggRing];
     if (own) {
-        float vs[NBM][2], sr_[2];
+        float vs[NBM][2];
 #pragma unroll
         for (int j = 0; j < NBM; ++j) {   // a slot without a node reads the bias row
             const int npj = __builtin_amdgcn_readlane(my_np, j);
@@ -2470,15 +2489,6 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
 #pragma unroll
             for (int u = 0; u < 2; ++u)
                 vs[j][u] = vrow[min(lane + kWave * u, M - 1)];
-        }
-        {
-            const bool ok = __builtin_amdgcn_readfirstlane(pv_ok);
-            const float *srow = g.mem_new + (int64_t)(ok ? pv : 0) * M;
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                sr_[u] = srow[min(lane + kWave * u, M - 1)];
-            if (!ok)
-                sr_[0] = sr_[1] = 0.f;
         }
         issue_fence();
         float sv[2] = {0.f, 0.f};   // sum_j alpha_j,head(d) seedV_j[d]
@@ -2574,19 +2584,17 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
                         sv[u] = (lane + kWave * u) / d_h == e0 + e ? sh[e][u] : sv[u];
                 }
         }
-        // [sum alpha seedV || s'_r || 0]
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int d = lane + kWave * u;
-            if (d < M) {
+            if (d < M)
                 AO[wave * SAO + d] = sv[u];
-                AO[wave * SAO + M + d] = sr_[u];
-            }
         }
-        for (int k = 2 * M + lane; k < OC * 16; k += kWave)
-            AO[wave * SAO + k] = 0.f;
     }
     // the value GEMM's first weight chunks load across the barrier
+    int again = lane;   // cn and q4 once more: held through phase 2 they would be spilled
+    asm volatile("" : "+v"(again));
+    const int col0 = again & 15, row0 = 4 * (again >> 4);
     const f4 *pwv = g.v_b + (int64_t)min(wave, VNB - 1) * kWave + lane;
     const int64_t vstep = (int64_t)VNB * kWave;
     if (wave < VNB)
@@ -2595,12 +2603,12 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
 
     // 3. value GEMM: [RT H x KF] abar rows x W_v,a^t, column block wave
     if (wave < VNB) {
-        const f4 acc = agg_gemm(As + cn * KFP + q4, pwv, vstep, KFC, ring);
-        const int col = wave * 16 + cn;
+        const f4 acc = agg_gemm(As + col0 * KFP + row0, pwv, vstep, KFC, ring);
+        const int col = wave * 16 + col0;
         if (col < M) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int row = q4 + v, rr = row / H, ee = row - rr * H;
+                const int row = row0 + v, rr = row / H, ee = row - rr * H;
                 if (rr < nroots && col / d_h == ee)
                     AO[rr * SAO + col] += acc[v];
             }
@@ -2614,13 +2622,13 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
 
     // 4. h = ReLU(W_o [o || s'_r] + b_o), column block wave
     if (wave < ONB) {
-        const f4 acc = agg_gemm(AO + cn * SAO + q4, pwo, ostep, OC, ring);
-        const int col = wave * 16 + cn;
+        const f4 acc = agg_gemm(AO + col0 * SAO + row0, pwo, ostep, OC, ring);
+        const int col = wave * 16 + col0;
         if (col < M) {
             const float bo = g.b_o[col];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int row = q4 + v;
+                const int row = row0 + v;
                 if (row < nroots)
                     g.h[(int64_t)(r0 + row) * M + col] = fmaxf(acc[v] + bo, 0.f);
             }
