@@ -2429,7 +2429,8 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
     const int cu = __builtin_amdgcn_readfirstlane(c);
     // filled slots whose event id is out of range: no edge features
     const uint64_t no_edge = __ballot(lane < cu && my_e < 0);
-    if (D_e > 0) {
+    // (a graph without events has no row 0 to clamp to: its efeat may be null)
+    if (D_e > 0 && g.E > 0) {
 #pragma unroll
         for (int j = 0; j < NBM; ++j) {
             const float *erow =
