@@ -28,6 +28,7 @@
 // 5.20 ms with products over slots and a launch (or two) per product, and
 // 1.81 ms with these, grouped eight launches to a step; one step at a batch
 // of 600: 919 and 229 us.
+// Rows too wide for a wavefront's registers take the products over slots.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -476,6 +477,147 @@ __global__ __launch_bounds__(256) void k_att_bwd(AttArgs a)
                         a.dKm[((int64_t)r * a.nb + j) * M + lane + kWave * i] = dk[j][i];
 }
 
+// The same attention by slots, for the trainers that slot_form names: every
+// slot's row [s'_u || efeat || phi], its key and value are stored, and the
+// products run over slots instead of (root, head) rows.  Rows of any width,
+// and a cost and work space that do not grow with the heads.
+struct SlotArgs {
+    int R, nb, M, D_e, D_t, H;
+    float scale;
+    const int32_t *cnt, *nbr_pos, *eid;
+    const double *root_ts, *nts, *omega, *beta;
+    const float *s_new, *efeat, *Q, *dXo;   // Q [R x M], dXo [R x 2M]
+    float *rows;                            // [R nb x Dkv], zero past the count
+    float *KV, *dKV;                        // [R nb x 2M]
+    float *alpha, *Xo, *dQ;                 // [R x H x nb], [R x 2M], [R x M]
+};
+
+// One wavefront per slot: its row
+__global__ __launch_bounds__(256) void k_slot_rows(SlotArgs a)
+{
+    const int64_t sl = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63, M = a.M, D_e = a.D_e, D_t = a.D_t;
+    if (sl >= (int64_t)a.R * a.nb)
+        return;
+    const int r = (int)(sl / a.nb), j = (int)(sl % a.nb), Dkv = M + D_e + D_t;
+    float *x = a.rows + sl * Dkv;
+    if (j >= a.cnt[r]) {
+        for (int k = lane; k < Dkv; k += kWave)
+            x[k] = 0.f;
+        return;
+    }
+    wave_copy_row(x, a.s_new + (int64_t)a.nbr_pos[sl] * M, M, lane);
+    if (D_e > 0)
+        wave_copy_row(x + M, a.efeat + (int64_t)a.eid[sl] * D_e, D_e, lane);
+    const double dt = a.root_ts[r] - a.nts[sl];
+    for (int d = lane; d < D_t; d += kWave)
+        x[M + D_e + d] = time_enc(a.omega[d], a.beta[d], dt);
+}
+
+// One wavefront per root, lanes over the outputs k = lane, lane + 64: per head
+// the scores q . K of its slots, their softmax alpha and o = sum_s alpha_s V_s.
+__global__ __launch_bounds__(256) void k_slot_fwd(SlotArgs a)
+{
+    const int r = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
+    const int lane = threadIdx.x & 63;
+    if (r >= a.R)
+        return;
+    const int M = a.M, H = a.H, nb = a.nb, dh = M / H;
+    const int cr = __builtin_amdgcn_readfirstlane(a.cnt[r]);
+    const float *kv = a.KV + (int64_t)r * nb * 2 * M;
+    float q[2], o[2] = {0.f, 0.f};
+    int head[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int k = lane + kWave * i;
+        q[i] = k < M ? a.Q[(int64_t)r * M + k] : 0.f;
+        head[i] = k < M ? k / dh : -1;
+    }
+    for (int eta = 0; eta < H && cr > 0; ++eta) {
+        float mine = -INFINITY;   // lane j < cr: the score of slot j
+        for (int j = 0; j < cr; ++j) {
+            float p = 0.f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (head[i] == eta)
+                    p = fmaf(q[i], kv[(int64_t)j * 2 * M + lane + kWave * i], p);
+            const float sc = wave_total(p) * a.scale;
+            mine = lane == j ? sc : mine;
+        }
+        const float mx = wave_max(mine);
+        const float ex = lane < cr ? expf(mine - mx) : 0.f;
+        const float al = ex / wave_total(ex);
+        if (lane < cr)
+            a.alpha[((int64_t)r * H + eta) * nb + lane] = al;
+        for (int j = 0; j < cr; ++j) {
+            const float aj = lane_value(al, j);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (head[i] == eta)
+                    o[i] = fmaf(aj, kv[(int64_t)j * 2 * M + M + lane + kWave * i], o[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if (lane + kWave * i < M)
+            a.Xo[(int64_t)r * 2 * M + lane + kWave * i] = o[i];
+}
+
+// Backward, the same layout: dalpha_s = do . V_s, the scores' gradients, dV_s
+// = alpha_s do, dK_s = dscore_s q, dq = sum_s dscore_s K_s; zero rows past the
+// count.
+__global__ __launch_bounds__(256) void k_slot_bwd(SlotArgs a)
+{
+    const int r = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
+    const int lane = threadIdx.x & 63;
+    if (r >= a.R)
+        return;
+    const int M = a.M, H = a.H, nb = a.nb, dh = M / H;
+    const int cr = __builtin_amdgcn_readfirstlane(a.cnt[r]);
+    const float *kv = a.KV + (int64_t)r * nb * 2 * M;
+    float *dkv = a.dKV + (int64_t)r * nb * 2 * M;
+    float q[2], g[2], dq[2] = {0.f, 0.f};
+    int head[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int k = lane + kWave * i;
+        q[i] = k < M ? a.Q[(int64_t)r * M + k] : 0.f;
+        g[i] = k < M ? a.dXo[(int64_t)r * 2 * M + k] : 0.f;
+        head[i] = k < M ? k / dh : -1;
+    }
+    for (int eta = 0; eta < H && cr > 0; ++eta) {
+        const float al = lane < cr ? a.alpha[((int64_t)r * H + eta) * nb + lane] : 0.f;
+        float da = 0.f;   // lane j < cr: dalpha of slot j
+        for (int j = 0; j < cr; ++j) {
+            float p = 0.f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (head[i] == eta)
+                    p = fmaf(g[i], kv[(int64_t)j * 2 * M + M + lane + kWave * i], p);
+            const float d = wave_total(p);
+            da = lane == j ? d : da;
+        }
+        const float dsc = al * (da - wave_total(al * da)) * a.scale;
+        for (int j = 0; j < cr; ++j) {
+            const float w = lane_value(dsc, j), aj = lane_value(al, j);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (head[i] == eta) {
+                    const int64_t k = (int64_t)j * 2 * M + lane + kWave * i;
+                    dq[i] = fmaf(w, kv[k], dq[i]);
+                    dkv[k] = w * q[i];
+                    dkv[k + M] = aj * g[i];
+                }
+        }
+    }
+    for (int k = max(cr, 0) * 2 * M + lane; k < nb * 2 * M; k += kWave)
+        dkv[k] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if (lane + kWave * i < M)
+            a.dQ[(int64_t)r * M + lane + kWave * i] = dq[i];
+}
+
 // ------------------------------------------- gradient of the new memories
 // The contributors sorted by node (a stable sort, so in contributor order
 // within a node) are summed in blocks of 64 sorted positions, one wavefront
@@ -762,6 +904,8 @@ struct tgm_trainer {
     float *Q = nullptr, *Xo = nullptr, *dO = nullptr, *dXo = nullptr,
           *dQ = nullptr;
     float *U = nullptr, *abar = nullptr, *dbar = nullptr;   // [R x H x ldu]; dbar: dabar, then du
+    bool slots = false;   // attention by slots (slot_form): the next three instead of U, abar, dbar
+    float *rows = nullptr, *KV = nullptr, *dKV = nullptr;
     float *alpha = nullptr, *dKm = nullptr, *ds = nullptr;
     float *X = nullptr, *Hm = nullptr, *Gx = nullptr, *Gh = nullptr, *dGx = nullptr,
           *dGh = nullptr;
@@ -838,6 +982,12 @@ tgm_status_t att_launch(bool bwd, const AttArgs &a, hipStream_t s)
 
 // Rows of up to 192 edge features and 128 time codes keep 10 slots (70
 // registers); wider ones take the larger row, 5 slots at a time.
+constexpr int kAttTimeCodes = 6 * kWave;   // at most
+
+// Whether a trainer's attention runs by slots: rows wider than a wavefront's
+// registers hold (D_e <= 256 always).
+bool slot_form(const tgm_model *m) { return m->D_t > kAttTimeCodes; }
+
 tgm_status_t att_dispatch(bool bwd, const AttArgs &a, hipStream_t s)
 {
     if (a.D_e <= 3 * kWave && a.D_t <= 2 * kWave)
@@ -856,7 +1006,7 @@ extern "C" tgm_status_t tgm_trainer_destroy(tgm_trainer_t tr)
     void *bufs[] = {tr->theta, tr->grad, tr->m1, tr->m2, tr->part, tr->Zs, tr->Zd, tr->dZsrc,
                     tr->dZdst, tr->act, tr->dsc, tr->lossv, tr->loss, tr->cq, tr->Q,
                     tr->Xo, tr->dO, tr->dXo, tr->dQ, tr->U, tr->abar, tr->dbar, tr->alpha,
-                    tr->dKm, tr->ds, tr->X, tr->Hm, tr->Gx, tr->Gh, tr->dGx, tr->dGh,
+                    tr->rows, tr->KV, tr->dKV, tr->dKm, tr->ds, tr->X, tr->Hm, tr->Gx, tr->Gh, tr->dGx, tr->dGh,
                     tr->ds_head, tr->ds_tail};
     for (void *b : bufs)
         (void)hipFree(b);
@@ -914,6 +1064,7 @@ extern "C" tgm_status_t tgm_trainer_create(tgm_model_t m, const tgm_weights *w,
     tr->n_params = tr->off[kNParams];
     const int64_t R = tr->max_roots, B = tr->max_b, S = R * nb, C = tr->max_nodes;
     const int64_t n_items = R + S, H = tr->H, blocks = cdiv(n_items, kWave);
+    tr->slots = slot_form(m);
     tr->ldu = round_up((int32_t)Dkv, 4);
     tr->ldx = round_up((int32_t)D_x, 4);
     int64_t part = 0;   // every split product and its row sums at kMaxSplits
@@ -945,9 +1096,15 @@ extern "C" tgm_status_t tgm_trainer_create(tgm_model_t m, const tgm_weights *w,
     alloc(&tr->dO, R * M);
     alloc(&tr->dXo, R * 2 * M);
     alloc(&tr->dQ, R * M);
-    alloc(&tr->U, R * H * tr->ldu);
-    alloc(&tr->abar, R * H * tr->ldu);
-    alloc(&tr->dbar, R * H * tr->ldu);
+    if (tr->slots) {
+        alloc(&tr->rows, S * Dkv);
+        alloc(&tr->KV, S * 2 * M);
+        alloc(&tr->dKV, S * 2 * M);
+    } else {
+        alloc(&tr->U, R * H * tr->ldu);
+        alloc(&tr->abar, R * H * tr->ldu);
+        alloc(&tr->dbar, R * H * tr->ldu);
+    }
     alloc(&tr->alpha, R * H * nb);
     alloc(&tr->dKm, S * M);
     alloc(&tr->ds, C * M);
@@ -1057,15 +1214,26 @@ tgm_status_t tgm::train_step_launch(tgm_trainer_t tr, tgm_model_t m, tgm_graph_t
     TGM_LAUNCH(k_train_rows,
                dim3((unsigned)(ra.n_root + ra.n_node + ra.n_key + cdiv(M, 4))), dim3(256), 0, s,
                ra);
-    // the predictor's layers, the queries and the GRU's gates
+    const SlotArgs sl{R, nb, M, tr->D_e, tr->D_t, H, 1.f / sqrtf((float)dh), sb.cnt, sb.nbr_pos,
+                      sb.eid, sb.root_ts, sb.nts, m->omega, m->beta, mem_new, g->efeat, tr->Q,
+                      tr->dXo, tr->rows, tr->KV, tr->dKV, tr->alpha, tr->Xo, tr->dQ};
+    const dim3 per_root((unsigned)cdiv((int64_t)R * kWave, 256));
+    if (tr->slots)
+        TGM_LAUNCH(k_slot_rows, dim3((unsigned)cdiv(S, 4)), dim3(256), 0, s, sl);
+    // the predictor's layers, the queries and the GRU's gates (by slots: the
+    // keys and values too)
     {
-        GemmProb g[5] = {mul(b, M, M, h, M, W_src, M, tr->Zs, M),
+        GemmProb g[7] = {mul(b, M, M, h, M, W_src, M, tr->Zs, M),
                          mul(2 * b, M, M, h_rest, M, W_dst, M, tr->Zd, M),
                          mul(R, M, M, s_v, 2 * M, W_q, Dq, tr->Q, M, tr->cq),
                          mul(cap, 3 * M, D_x, tr->X, ldx, W_ih, D_x, tr->Gx, 3 * M, b_ih),
                          mul(cap, 3 * M, M, tr->Hm, M, W_hh, M, tr->Gh, 3 * M, b_hh)};
         g[3].live = g[4].live = sb.n_nodes;
-        TGM_TRY_STATUS(gemm_launch(false, true, g, 5, s));
+        if (tr->slots) {
+            g[5] = mul((int)S, M, Dkv, tr->rows, Dkv, W_k, Dkv, tr->KV, 2 * M, b_k);
+            g[6] = mul((int)S, M, Dkv, tr->rows, Dkv, W_v, Dkv, tr->KV + M, 2 * M, b_v);
+        }
+        TGM_TRY_STATUS(gemm_launch(false, true, g, tr->slots ? 7 : 5, s));
     }
     PredArgs pa{b, M, tr->Zs, tr->Zd, tr->p(14), tr->p(15), tr->p(16), tr->dZsrc, tr->dZdst,
                 tr->act, tr->dsc, tr->lossv};
@@ -1081,13 +1249,16 @@ tgm_status_t tgm::train_step_launch(tgm_trainer_t tr, tgm_model_t m, tgm_graph_t
         g[1].gate = h;
         g[2].gate = h_rest;
         g[1].ldg = g[2].ldg = M;
-        TGM_TRY_STATUS(gemm_launch(false, false, g, 3, s));
+        const int u = tr->slots ? 1 : 0;   // (no u by slots)
+        TGM_TRY_STATUS(gemm_launch(false, false, g + u, 3 - u, s));
     }
     AttArgs aa{R, nb, M, tr->D_e, tr->D_t, H, ldu, 1.f / sqrtf((float)dh), sb.cnt, sb.root_pos,
                sb.nbr_pos, sb.eid, sb.root_ts, sb.nts, m->omega, m->beta, mem_new, g->efeat,
                tr->U, tr->alpha, tr->abar, tr->dbar, tr->dKm};
-    TGM_TRY_STATUS(att_dispatch(false, aa, s));
-    {   // o = W_v abar + b_v per head (zero without neighbours)
+    if (tr->slots) {
+        TGM_LAUNCH(k_slot_fwd, per_root, dim3(256), 0, s, sl);
+    } else {   // o = W_v abar + b_v per head (zero without neighbours)
+        TGM_TRY_STATUS(att_dispatch(false, aa, s));
         GemmProb p = heads(mul(R, dh, Dkv, tr->abar, H * ldu, W_v, Dkv, tr->Xo, 2 * M, b_v), H,
                            ldu, (int64_t)dh * Dkv, dh, dh);
         p.row_on = sb.cnt;
@@ -1100,18 +1271,24 @@ tgm_status_t tgm::train_step_launch(tgm_trainer_t tr, tgm_model_t m, tgm_graph_t
         p.zero_cols = M;
         TGM_TRY_STATUS(gemm_launch(false, false, &p, 1, s));
     }
-    {   // dabar = W_v^t do per head
+    GemmProb v = mul(R, M, M, tr->dQ, M, W_q, Dq, tr->dXo + M, 2 * M);   // the query's part
+    v.accumulate = 1;
+    if (tr->slots) {   // dq, dK and dV; then the slots' gradient of s'_u and the roots' of s'_v
+        TGM_LAUNCH(k_slot_bwd, per_root, dim3(256), 0, s, sl);
+        const GemmProb k = mul((int)S, M, M, tr->dKV, 2 * M, W_k, Dkv, tr->dKm, M);
+        TGM_TRY_STATUS(gemm_launch(false, false, &k, 1, s));
+        GemmProb p[2] = {mul((int)S, M, M, tr->dKV + M, 2 * M, W_v, Dkv, tr->dKm, M), v};
+        p[0].accumulate = 1;
+        TGM_TRY_STATUS(gemm_launch(false, false, p, 2, s));
+    } else {   // dabar = W_v^t do per head
         const GemmProb p = heads(mul(R, Dkv, dh, tr->dXo, 2 * M, W_v, Dkv, tr->dbar, H * ldu), H,
                                  dh, (int64_t)dh * Dkv, ldu);
         TGM_TRY_STATUS(gemm_launch(false, false, &p, 1, s));
-    }
-    TGM_TRY_STATUS(att_dispatch(true, aa, s));
-    {   // dq = W_k du per head, then its part of the roots' gradient of s'_v
-        GemmProb p = heads(mul(R, dh, Dkv, tr->dbar, H * ldu, W_k, Dkv, tr->dQ, M), H, ldu,
-                           (int64_t)dh * Dkv, dh);
-        TGM_TRY_STATUS(gemm_launch(false, true, &p, 1, s));
-        GemmProb v = mul(R, M, M, tr->dQ, M, W_q, Dq, tr->dXo + M, 2 * M);
-        v.accumulate = 1;
+        TGM_TRY_STATUS(att_dispatch(true, aa, s));
+        // dq = W_k du per head, then its part of the roots' gradient of s'_v
+        const GemmProb q = heads(mul(R, dh, Dkv, tr->dbar, H * ldu, W_k, Dkv, tr->dQ, M), H, ldu,
+                                 (int64_t)dh * Dkv, dh);
+        TGM_TRY_STATUS(gemm_launch(false, true, &q, 1, s));
         TGM_TRY_STATUS(gemm_launch(false, false, &v, 1, s));
     }
     // each node's gradient: its contributors' rows, sorted by node
@@ -1128,22 +1305,27 @@ tgm_status_t tgm::train_step_launch(tgm_trainer_t tr, tgm_model_t m, tgm_graph_t
     // (a batch's node set has about as many nodes as roots: hubs recur)
     const int nodes = std::min(cap, R + R / 2);
     float *at = tr->part;
+    const int64_t kv_rows = tr->slots ? cdiv(M, 64) * S : H * cdiv(dh, 64) * R;
     const int64_t tiles = cdiv(3 * M, 64) * (cdiv(D_x, 64) + cdiv(M, 112)) * nodes +
-                          (2 * H * cdiv(dh, 64) * cdiv(Dkv, 112) + 3 * cdiv(M, 64)) * R;
+                          2 * cdiv(Dkv, 112) * kv_rows + 3 * cdiv(M, 64) * R;
     const int len = (int)std::max<int64_t>(kMinSplit, tiles / kGradBlocks);
     GemmProb w[9] = {
         grad_of(3 * M, D_x, cap, nodes, len, tr->dGx, 3 * M, tr->X, ldx, &at),
         grad_of(3 * M, M, cap, nodes, len, tr->dGh, 3 * M, tr->Hm, M, &at),
         grad_of(M, M, R, R, len, tr->dQ, M, s_v, 2 * M, &at),
-        grad_of(dh, Dkv, R, R, len, tr->Q, M, tr->dbar, H * ldu, &at, H),
-        grad_of(dh, Dkv, R, R, len, tr->dXo, 2 * M, tr->abar, H * ldu, &at, H),
+        tr->slots ? grad_of(M, Dkv, (int)S, (int)S, len, tr->dKV, 2 * M, tr->rows, Dkv, &at)
+                  : grad_of(dh, Dkv, R, R, len, tr->Q, M, tr->dbar, H * ldu, &at, H),
+        tr->slots ? grad_of(M, Dkv, (int)S, (int)S, len, tr->dKV + M, 2 * M, tr->rows, Dkv, &at)
+                  : grad_of(dh, Dkv, R, R, len, tr->dXo, 2 * M, tr->abar, H * ldu, &at, H),
         grad_of(M, 2 * M, R, R, len, tr->dO, M, tr->Xo, 2 * M, &at),
         grad_of(M, M, b, b, len, tr->dZsrc, M, h, M, &at),
         grad_of(M, M, 2 * b, 2 * b, len, tr->dZdst, M, h_rest, M, &at),
         grad_of(1, M, 2 * b, 2 * b, len, tr->dsc, 1, tr->act, M, &at)};
     w[0].live = w[1].live = sb.n_nodes;
-    w[3].sA = w[4].sA = dh;
-    w[3].sB = w[4].sB = ldu;
+    if (!tr->slots) {
+        w[3].sA = w[4].sA = dh;
+        w[3].sB = w[4].sB = ldu;
+    }
     TGM_TRY_STATUS(gemm_launch(true, false, w, 9, s));
     tr->steps++;
     FinishArgs f{};
