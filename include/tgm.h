@@ -422,6 +422,10 @@ typedef struct {
  * copied into its device parameter vector; it owns the gradient, the
  * optimizer's moments and the work space for batches of up to
  * max_roots / 3 events and node sets of up to max_nodes rows (m's limits).
+ * Its largest arrays hold 3 max_roots H (M + D_e + D_t) floats; with many
+ * heads (32 or more, 8 or more where a root's nb rows do not fit a wavefront's
+ * registers: nb > 10, or > 5 for D_e > 192 or D_t > 128) or D_t > 384
+ * max_roots nb (5 M + D_e + D_t).
  * The trainer rewrites m's operands after every step: m must not be used by
  * another trainer.  Errors: TGM_EINVAL (null, JODIE model, parameters),
  * TGM_ENOMEM, TGM_EDEVICE. */

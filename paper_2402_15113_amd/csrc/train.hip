@@ -28,7 +28,8 @@
 // 5.20 ms with products over slots and a launch (or two) per product, and
 // 1.81 ms with these, grouped eight launches to a step; one step at a batch
 // of 600: 919 and 229 us.
-// Rows too wide for a wavefront's registers take the products over slots.
+// Rows too wide for a wavefront's registers, and many heads, take the products
+// over slots (slot_form).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -984,15 +985,38 @@ tgm_status_t att_launch(bool bwd, const AttArgs &a, hipStream_t s)
 // registers); wider ones take the larger row, 5 slots at a time.
 constexpr int kAttTimeCodes = 6 * kWave;   // at most
 
-// Whether a trainer's attention runs by slots: rows wider than a wavefront's
-// registers hold (D_e <= 256 always).
-bool slot_form(const tgm_model *m) { return m->D_t > kAttTimeCodes; }
+bool att_narrow(int D_e, int D_t) { return D_e <= 3 * kWave && D_t <= 2 * kWave; }
+int att_slots(int D_e, int D_t) { return att_narrow(D_e, D_t) ? 10 : 5; }
 
 tgm_status_t att_dispatch(bool bwd, const AttArgs &a, hipStream_t s)
 {
-    if (a.D_e <= 3 * kWave && a.D_t <= 2 * kWave)
+    if (att_narrow(a.D_e, a.D_t))
         return att_launch<3, 2, 10>(bwd, a, s);
     return att_launch<4, 6, 5>(bwd, a, s);
+}
+
+// Whether a trainer's attention runs by slots: rows wider than a wavefront's
+// registers hold (D_e <= 256 always), and many heads.  Over (root, head) rows
+// both the cost and the work space grow with the heads, by slots hardly
+// (three arrays of R H ldu floats against R nb (Dkv + 4 M)), and rows that
+// stay in the registers for all heads grow less than those loaded again for
+// each.  A step in us, (root, head) rows / slots, M = 100, 172 or 186 edge
+// features, 100 time codes:
+//   10 slots (in registers)  600 events, 10 heads 340 / 417, 20: 462 / 486,
+//     25: 520 / 523, 50: 881 / 709;  2,400 events, 10: 794 / 886, 20:
+//     1,227 / 1,031, 50: 2,763 / 1,491
+//   20 slots (loaded again)  600 events, 5: 478 / 570, 10: 741 / 667, 20:
+//     1,243 / 835;  2,400 events, 5: 1,138 / 1,387, 10: 1,951 / 1,551, 20:
+//     3,555 / 1,849
+// At M = 8, 32 and 128, 8 heads and 20 slots: 334 / 266, 371 / 319 and 560 /
+// 583 (600 events); at 64 slots 10 heads lie just past the line (1,789 /
+// 1,996), 20 well past it (3,295 / 2,687).
+constexpr int kSlotHeads = 32, kSlotHeadsAgain = 8;   // from so many heads on
+
+bool slot_form(const tgm_model *m)
+{
+    return m->D_t > kAttTimeCodes ||
+           m->H >= (m->nb > att_slots(m->D_e, m->D_t) ? kSlotHeadsAgain : kSlotHeads);
 }
 
 }  // namespace

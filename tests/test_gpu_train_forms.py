@@ -1,7 +1,8 @@
 """The training attention's two forms at the edges of their ranges, against the
 fp64 oracle: rows of up to 384 time codes stay in a wavefront's registers and
-the products run over (root, head) rows, wider ones take the products over
-slots.  Also the wide rows (more than 192 edge features) with more slots than
+the products run over (root, head) rows; wider ones take the products over
+slots, and so do 8 heads or more whose rows are loaded again for each head
+(more than 10 slots, or 5 of wide rows) and 32 or more whose rows are not.  Also the wide rows (more than 192 edge features) with more slots than
 they keep at a time, whose heads' sums go through memory.  Tolerances: the
 training tests' (tests/test_gpu_train.py)."""
 import pytest
@@ -40,4 +41,12 @@ def test_time_code_widths(orc, M, H, D_e, D_t, B, nb):
 @pytest.mark.parametrize("M,H,D_e,D_t,B,nb", [
     (36, 3, 193, 33, 20, 6), (128, 4, 256, 20, 15, 17), (64, 2, 200, 140, 20, 64)])
 def test_wide_rows_in_parts(orc, M, H, D_e, D_t, B, nb):
+    pair(orc, M, H, D_e, D_t, B, nb)
+
+
+@pytest.mark.parametrize("M,H,D_e,D_t,B,nb", [
+    (14, 7, 5, 9, 25, 11), (16, 8, 5, 9, 25, 11), (16, 8, 5, 9, 25, 10), (64, 8, 17, 129, 25, 5),
+    (64, 8, 17, 129, 25, 6), (62, 31, 8, 16, 25, 10), (64, 32, 8, 16, 25, 10),
+    (48, 48, 0, 8, 40, 10), (120, 24, 30, 40, 30, 64), (32, 8, 0, 4, 200, 20)])
+def test_head_counts(orc, M, H, D_e, D_t, B, nb):
     pair(orc, M, H, D_e, D_t, B, nb)
