@@ -45,7 +45,7 @@ def projection_close(name, g, r, w):
     g = np.asarray(g, np.float64)
     err = np.abs(g - r.h)
     tol = ATOL * np.maximum(1.0, np.abs(f)) + RTOL * np.abs(r.h)
-    bad = err > tol
+    bad = ~(err <= tol)   # (NaN is outside)
     if bad.any():
         k = np.unravel_index(np.argmax(err - tol), err.shape)
         raise AssertionError(f"{name}: {int(bad.sum())}/{bad.size} outside tolerance; worst at "

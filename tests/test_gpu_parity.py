@@ -36,7 +36,7 @@ def close(name, g, o):
     o = np.asarray(o, dtype=np.float64)
     assert g.shape == o.shape, (name, g.shape, o.shape)
     err = np.abs(g - o)
-    bad = err > ATOL + RTOL * np.abs(o)
+    bad = ~(err <= ATOL + RTOL * np.abs(o))   # (NaN is outside)
     if bad.any():
         k = np.unravel_index(np.argmax(err - (ATOL + RTOL * np.abs(o))), err.shape)
         raise AssertionError(f"{name}: {int(bad.sum())}/{bad.size} outside tolerance; worst at "

@@ -87,7 +87,7 @@ def grad_check(gg, og, margin, stats):
         stats[k] = max(stats.get(k, 0.0), fro)
         err = np.abs(g - o)
         tol = 1e-4 * np.abs(o) + 1e-4 * np.abs(o).max()
-        bad = err > tol
+        bad = ~(err <= tol)   # (NaN is outside)
         if not bad.any():
             continue
         j = int(np.argmax(err - tol))
@@ -116,7 +116,7 @@ def scaled_close(name, g, o):
         return 0.0
     err = np.abs(g - o)
     tol = ATOL + RTOL * np.abs(o) + 1e-4 * np.abs(o).max()
-    bad = err > tol
+    bad = ~(err <= tol)   # (NaN is outside)
     if bad.any():
         k = np.unravel_index(np.argmax(err - tol), err.shape)
         raise AssertionError(f"{name}: {int(bad.sum())}/{bad.size} outside the scaled tolerance; "
