@@ -130,16 +130,17 @@ struct Operand {
             }
     }
     // the last step, whose first `skip` elements of k the step before had:
-    // zeros there (in A only, so their products vanish)
+    // zeros there (in both operands: zero times an infinity is no zero)
     template <int S>
     __device__ __forceinline__ void skip_first(int skip, int tid)
     {
         const int t = min(tid, TH - 1), r = t / PER, c = 4 * (t % PER);
+        if ((KC ? c : r) < skip)
 #pragma unroll
-        for (int u = 0; u < NV; ++u)
+            for (int u = 0; u < NV; ++u)
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
-                v[S][u][x] = (KC ? c + x : r + PU * u) < skip ? 0.f : v[S][u][x];
+                for (int x = 0; x < 4; ++x)
+                    v[S][u][x] = (KC ? c + x : r + PU * u) < skip ? 0.f : v[S][u][x];
     }
     // E consecutive k from `k` on of row or column c
     template <int E>
@@ -258,8 +259,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &p, int m0, int n0, int
                 compute(i, lds);
                 if (i + 1 >= steps)
                     break;
-                if (skip > 0 && i + 2 == steps)
+                if (skip > 0 && i + 2 == steps) {
                     a.template skip_first<1>(skip, tid);
+                    b.template skip_first<1>(skip, tid);
+                }
                 a.template store<1>(lds + kBuf);
                 b.template store<1>(lds + kBuf + OA::kFloats);
                 lds_barrier();
@@ -270,8 +273,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &p, int m0, int n0, int
                 compute(i + 1, lds + kBuf);
                 if (i + 2 >= steps)
                     break;
-                if (skip > 0 && i + 3 == steps)
+                if (skip > 0 && i + 3 == steps) {
                     a.template skip_first<0>(skip, tid);
+                    b.template skip_first<0>(skip, tid);
+                }
                 a.template store<0>(lds);
                 b.template store<0>(lds + OA::kFloats);
                 lds_barrier();

@@ -36,3 +36,20 @@ def test_training_products_at_tile_edges(orc, M, H, D_e, D_t, B, nb):
     w = make_weights(wl.M, wl.D_e, wl.D_t, seed=6, beta="random")
     print(f"[gemm] M={M} H={H} D_e={D_e} D_t={D_t} B={B} nb={nb}", flush=True)
     train_pair(orc, wl, w, make_predictor(wl.M, seed=3), wl.n_iters, s=wl.s, lr=1e-3)
+
+
+def test_infinite_weights_in_the_overlapped_step(orc):
+    """A reduction's last step of 32 overlaps the one before where its length
+    is no multiple of 32 (62: elements 30 and 31 are in both).  An infinite
+    weight there, of an update gate and an edge feature, saturates the gate; it
+    is no NaN."""
+    import numpy as np
+
+    from test_gpu_apan import apan_pair
+    from test_gpu_parity import tie_heavy
+    wl = tie_heavy(7, N=30, E=200, M=8, H=1, D_e=40, D_t=6, B=20, nb=4)
+    w = make_weights(wl.M, wl.D_e, wl.D_t, seed=2, beta="random", model="apan", K_mb=4)
+    W = np.array(w.W_ih, dtype=np.float32)   # [3 M x 62]: mail (16 + 40), time codes
+    W[wl.M + 1, 30], W[wl.M + 3, 31] = np.inf, -np.inf
+    w.W_ih = W
+    apan_pair(orc, wl, w, wl.n_iters)
