@@ -261,7 +261,10 @@ __device__ __forceinline__ void gru_body(const GruArgs &g, float *lds, int *s_ha
     gw.KXC = KXC;
     const int j = wave & 3, half = wave >> 2;
     // k_gru_w's halves (its k range is padded to whole rings), so that both
-    // kernels add in the same order and give the same bits
+    // kernels add in the same order and give the same bits; for the shapes that
+    // k_gru_w does not take they are no slower than halves of equal length
+    // (update calls of 2,000 events: 9 chunks as 8 + 1 33.6 us, as 4 + 5 33.7;
+    // 10 as 8 + 2 36.5, as 5 + 5 36.6; 14 as 8 + 6 40.2, as 7 + 7 41.3)
     const int kmid = min(gw_chunks(KC) / 2, KC);
     const int kc0 = half ? kmid : 0, kc1 = half ? KC : kmid;
     gw.last = max(kc1 - 1, 0);
@@ -3148,10 +3151,15 @@ tgm_status_t update_begin(tgm_state_t st, tgm_model_t m, tgm_graph_t g, int64_t 
         if (inplace_nodes && (!w_ok || !phi_ready || !new_mem_ts))
             return TGM_EINVAL;   // only the resident-weights GRU reads in place
         // Where the fetch has formed phi (the executor), the resident-weight
-        // GRU; a call on its own would launch k_phi for it, and k_gru, which
-        // forms phi itself, is faster then at every size (update of 2,200
-        // nodes 29.9 against 33.2 us, 9,200 nodes 71 against 77, 16,200 nodes
-        // 113 against 124; D_m = 372).
+        // GRU; a call on its own would launch k_phi for it, and k_gru forms phi
+        // itself.  Whole update calls, k_gru / k_phi and k_gru_w, in us, for
+        // batches of 50, 600 and 4,000 events with 10 neighbours, N = 16,682:
+        //   D_m = 372, D_t = M = 100   25.7 / 28.9, 54.6 / 56.7, 91.2 / 98.4
+        //   D_m = 356, M = 128         25.1 / 28.4, 52.8 / 57.4, 88.6 / 97.2
+        //   D_m = 200, M = 100         23.0 / 26.4, 45.6 / 49.3, 74.7 / 85.8
+        //   D_m = 128, M = 64          20.3 / 22.3, 26.7 / 32.3, 47.1 / 46.2
+        //   D_m = 64, M = 32           18.7 / 21.1, 22.2 / 24.7, 34.3 / 33.7
+        // Narrow rows of many nodes are up to 3% slower, all else is faster.
         if (w_ok && (phi_ready || jodie)) {
             // phi once per node (unless the fetch formed it), then MB hidden
             // blocks x (kGruGrid / MB) row ranges (kGruGrid % MB workgroups idle)
