@@ -524,14 +524,16 @@ struct tgm_apan {
     int32_t max_batch = 0, max_nodes = 0, propagate = 1;
     // weights (plain, device)
     float *W_ih = nullptr, *W_hh = nullptr, *b_ih = nullptr, *b_hh = nullptr;
-    float *W_q = nullptr, *b_q = nullptr, *W_k = nullptr, *b_k = nullptr;
-    double *omega = nullptr, *beta = nullptr, *cq = nullptr;   // cq: W_q phi(0) + b_q
+    double *omega = nullptr, *beta = nullptr;
     // committed tables
     float *mem = nullptr, *mb = nullptr;
     double *mem_ts = nullptr, *mb_ts = nullptr;
     int32_t *ver = nullptr, *head = nullptr, *cnt = nullptr;
     // fetched rows of the last step and the updater's work space
     float *Wqk = nullptr, *c_u = nullptr;   // the key projection with the query's folded in
+    // what they are folded from, freed by the end of creation; cq: W_q phi(0) + b_q
+    float *W_q = nullptr, *b_q = nullptr, *W_k = nullptr;
+    double *cq = nullptr;
     float *f_mem = nullptr, *f_mb = nullptr, *U = nullptr, *X = nullptr, *Gx = nullptr,
           *Gh = nullptr;
     double *f_mem_ts = nullptr, *f_mb_ts = nullptr, *t_new = nullptr;
@@ -592,9 +594,9 @@ extern "C" tgm_status_t tgm_apan_destroy(tgm_apan_t a)
 {
     if (!a)
         return TGM_EINVAL;
-    void *bufs[] = {a->W_ih, a->W_hh, a->b_ih, a->b_hh, a->W_q, a->b_q, a->W_k, a->b_k,
-                    a->omega, a->beta, a->mem, a->mb, a->mem_ts, a->mb_ts, a->ver, a->head,
-                    a->cnt, a->Wqk, a->c_u, a->cq, a->f_mem, a->f_mb, a->U, a->X, a->Gx, a->Gh,
+    void *bufs[] = {a->W_ih, a->W_hh, a->b_ih, a->b_hh, a->W_q, a->b_q, a->W_k, a->omega,
+                    a->beta, a->mem, a->mb, a->mem_ts, a->mb_ts, a->ver, a->head, a->cnt,
+                    a->Wqk, a->c_u, a->cq, a->f_mem, a->f_mb, a->U, a->X, a->Gx, a->Gh,
                     a->f_mem_ts, a->f_mb_ts, a->t_new, a->f_ver, a->f_cnt, a->r_flag, a->r_node,
                     a->r_mem, a->r_ts, a->d_node, a->d_rank, a->d_keep, a->d_mail, a->d_t};
     for (void *b : bufs)
@@ -646,7 +648,6 @@ extern "C" tgm_status_t tgm_apan_create(const tgm_apan_desc *d, const tgm_weight
     alloc(&a->W_q, M * (M + D_t));
     alloc(&a->b_q, M);
     alloc(&a->W_k, M * D_x);
-    alloc(&a->b_k, M);
     alloc(&a->omega, D_t);
     alloc(&a->beta, D_t);
     alloc(&a->mem, N * M);
@@ -693,8 +694,8 @@ extern "C" tgm_status_t tgm_apan_create(const tgm_apan_desc *d, const tgm_weight
         } up[] = {{a->W_ih, w->W_ih, 4 * (size_t)(3 * M * D_x)}, {a->W_hh, w->W_hh, 4 * (size_t)(3 * M * M)},
                   {a->b_ih, w->b_ih, 4 * (size_t)(3 * M)}, {a->b_hh, w->b_hh, 4 * (size_t)(3 * M)},
                   {a->W_q, w->W_q, 4 * (size_t)(M * (M + D_t))}, {a->b_q, w->b_q, 4 * (size_t)M},
-                  {a->W_k, w->W_k, 4 * (size_t)(M * D_x)}, {a->b_k, w->b_k, 4 * (size_t)M},
-                  {a->omega, w->omega, 8 * (size_t)D_t}, {a->beta, w->beta, 8 * (size_t)D_t}};
+                  {a->W_k, w->W_k, 4 * (size_t)(M * D_x)}, {a->omega, w->omega, 8 * (size_t)D_t},
+                  {a->beta, w->beta, 8 * (size_t)D_t}};
         for (const auto &u : up)
             if (st == TGM_OK && u.bytes > 0)
                 st = upload(u.dst, u.src, u.bytes);
@@ -711,6 +712,13 @@ extern "C" tgm_status_t tgm_apan_create(const tgm_apan_desc *d, const tgm_weight
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
             st = TGM_EDEVICE;
     }
+    // (b_k, which shifts all of a node's scores alike, is not needed at all)
+    (void)hipFree(a->W_q);
+    (void)hipFree(a->b_q);
+    (void)hipFree(a->W_k);
+    (void)hipFree(a->cq);
+    a->W_q = a->b_q = a->W_k = nullptr;
+    a->cq = nullptr;
     if (st != TGM_OK) {
         tgm_apan_destroy(a);
         return st;
