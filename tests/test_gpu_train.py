@@ -288,3 +288,45 @@ def test_trainer_argument_errors():
         tgm.tgm_trainer_create(st.m, w, make_predictor(wl.M), opt="adam", beta1=1.5)
     assert e.value.code == tgm.TGM_EINVAL
     st.close()
+
+
+@pytest.mark.parametrize("opt,lr", [("sgd", 1.0), ("adam", 1e-2)])
+def test_optimizer_moves_every_parameter(orc, opt, lr):
+    """What the optimizer adds to the parameters, tensor by tensor, over the
+    first steps: ||(p - p0) - (oracle's)|| <= 2e-2 ||oracle's|| + the rounding of
+    the steps (2^-24 |p| an element and step), which the steps are large enough
+    to exceed: an optimizer that does nothing fails.  (The gradients are within
+    1e-4; Adam's first steps divide by them, eps = 1e-6 keeps those that are
+    rounding out.)  b_k, whose gradient is zero, must stay."""
+    from paper_2402_15113_amd.stage import from_workload
+    from test_gpu_parity import synthetic_state
+    wl = make_workload("tiny", E=4000, s=0)
+    w = make_weights(wl.M, wl.D_e, wl.D_t, beta="random")
+    tr = dict(predictor=make_predictor(wl.M, seed=1), opt=opt, lr=lr, eps=1e-6)
+    st = from_workload(wl, w, training=tr)
+    o = orc.Oracle(wl, w, training=tr)
+    tab = synthetic_state(wl, 4, 3)   # every tensor has a gradient from the first step on
+    st.load_state(4, **tab)
+    o.set_state(4, **tab)
+    p0 = split(st.train_state()["params"], st.param_sizes)
+    moved = set()
+    for i in range(4, 8):
+        print(f"[train] displacement {opt} iter {i}", flush=True)
+        st.step(i)
+        r = o.step()
+        if r.relu_margin < RELU_TAU:
+            break
+        gp, op = split(st.train_state()["params"], st.param_sizes), o.split(r.params)
+        for k in PARAM_NAMES:
+            d, e = gp[k] - p0[k], np.asarray(op[k], np.float64) - p0[k]
+            size = np.linalg.norm(e)
+            if k == "b_k":
+                assert not d.any(), k
+                continue
+            rounding = (i - 3) * 2.0 ** -24 * max(np.linalg.norm(gp[k]), np.linalg.norm(p0[k]))
+            assert size > 10 * rounding, (k, size, rounding)
+            err = np.linalg.norm(d - e)
+            assert err <= 2e-2 * size + rounding, (k, err / size)
+            moved.add(k)
+    assert moved == set(PARAM_NAMES) - {"b_k"}, moved
+    st.close()
