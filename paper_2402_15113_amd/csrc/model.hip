@@ -2201,8 +2201,8 @@ __global__ __launch_bounds__(512) void k_attn_fold_gather(AttnArgs g, int n_attn
 //   4. output GEMM h = ReLU(W_o [o || s'_r] + b_o).
 // LDS: 2 x 16 rows of the slot-row width and 16 rows of [o || s'_r], about
 // 53 KB at the GDELT-shaped sizes, so that two workgroups share a CU.
-constexpr int kAggMaxKF = 320;  // slot-row width
-constexpr int kAggTCols = 2;    // time codes per lane (D_t <= 128)
+constexpr int kAggCols = 5;     // slot-row columns per lane (KF <= 320)
+constexpr int kAggTCols = 2;    // of them time codes (D_t <= 128)
 constexpr int kAggDC = 7;       // 16-wide chunks of M (M <= 112)
 constexpr int kAggUT = 3;       // U tiles per wave (KFC <= 24)
 constexpr int kAggMaxH = 4;
@@ -2276,9 +2276,14 @@ __device__ __forceinline__ void agg_ring_load(const f4 *pw, int64_t bstep, int K
         ring[i] = pw[min(i, KC - 1) * bstep];
 }
 
-// NBM: slots per root held in registers (nb <= NBM, even); CE: 64-wide groups
-// of edge features (D_e <= 64 CE)
-template <int NBM, int CE>
+// NBM: slots per root held in registers (nb <= NBM, even).  A lane holds five
+// columns of a slot row: up to 192 edge features and 128 time codes in groups
+// of their own (lane + 64 i of each), wider edge features (PACKED) as columns
+// lane + 64 i of [phi || efeat], one of the groups mixed.  (Groups of their own
+// for those too, six columns, cost a wave per SIMD: 12,000 roots of 193
+// features and 10 slots took 131 us against 106, 256 features and 3 slots 228
+// against 159.)
+template <int NBM, bool PACKED>
 __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, int bid)
 {
     const int RT = g.RT;
@@ -2427,8 +2432,9 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
     // are all taken here and in the scores (128, four waves per SIMD): with
     // s'_r, cn, q4 and the event ids held through both, six were spilled, 15 MB
     // written and read back per 12,000 roots (109.6 against 104.2 us).
-    constexpr int CT = kAggTCols, CX = CE + CT;
-    float xs[NBM][CX];   // slot j's edge features lane + 64 i, then its time codes
+    constexpr int CX = kAggCols, CT = kAggTCols, CE = PACKED ? CX : CX - CT;
+    constexpr int T0 = PACKED ? 0 : CE;   // the time codes' first column
+    float xs[NBM][CX];   // slot j's edge features, then its time codes (PACKED: both)
     const int cu = __builtin_amdgcn_readfirstlane(c);
     // filled slots whose event id is out of range: no edge features
     const uint64_t no_edge = __ballot(lane < cu && my_e < 0);
@@ -2440,7 +2446,7 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
                 g.efeat + (int64_t)max(__builtin_amdgcn_readlane(my_e, j), 0) * D_e;
 #pragma unroll
             for (int i = 0; i < CE; ++i)
-                xs[j][i] = erow[min(lane + kWave * i, D_e - 1)];
+                xs[j][i] = erow[min(PACKED ? max(lane + kWave * i - D_t, 0) : lane + kWave * i, D_e - 1)];
         }
     } else {
 #pragma unroll
@@ -2458,16 +2464,19 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
             if (kWave * i >= D_t) {
 #pragma unroll
                 for (int j = 0; j < NBM; ++j)
-                    xs[j][CE + i] = 0.f;
+                    if (!PACKED)
+                        xs[j][T0 + i] = 0.f;
                 continue;
             }
             const int k = min(lane + kWave * i, D_t - 1);
+            const bool phi = !PACKED || lane + kWave * i < D_t;
             const double om = g.omega[k], be = g.beta[k];
 #pragma unroll
             for (int j = 0; j < NBM; ++j) {
                 const unsigned l = (unsigned)__builtin_amdgcn_readlane(dlo, j);
                 const long long h = __builtin_amdgcn_readlane(dhi, j);
-                xs[j][CE + i] = time_enc(om, be, __longlong_as_double((h << 32) | l));
+                const float x = time_enc(om, be, __longlong_as_double((h << 32) | l));
+                xs[j][T0 + i] = phi ? x : xs[j][T0 + i];
             }
         }
     }
@@ -2477,7 +2486,8 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
             if ((no_edge >> j) & 1)
 #pragma unroll
                 for (int i = 0; i < CE; ++i)
-                    xs[j][i] = 0.f;
+                    if (!PACKED || lane + kWave * i >= D_t)
+                        xs[j][i] = 0.f;
     __syncthreads();
 
     // 2. scores, softmax, aggregates (own root), two heads at a time; the value
@@ -2505,11 +2515,11 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
                 const float *us = Us + (wave * H + min(e0 + e, H - 1)) * KFP;
 #pragma unroll
                 for (int i = 0; i < CE; ++i) {
-                    const float x = us[min(D_t + lane + kWave * i, KF - 1)];
-                    uu[e][i] = lane + kWave * i < D_e && e0 + e < H ? x : 0.f;
+                    const float x = us[min((PACKED ? 0 : D_t) + lane + kWave * i, KF - 1)];
+                    uu[e][i] = lane + kWave * i < (PACKED ? KF : D_e) && e0 + e < H ? x : 0.f;
                 }
 #pragma unroll
-                for (int i = 0; i < CT; ++i) {
+                for (int i = 0; i < (PACKED ? 0 : CT); ++i) {
                     const float x = us[min(lane + kWave * i, KF - 1)];
                     uu[e][CE + i] = lane + kWave * i < D_t && e0 + e < H ? x : 0.f;
                 }
@@ -2575,10 +2585,10 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
                     float *as = As + (wave * H + e0 + e) * KFP;
 #pragma unroll
                     for (int i = 0; i < CE; ++i)
-                        if (lane + kWave * i < D_e)
-                            as[D_t + lane + kWave * i] = ab[e][i];
+                        if (lane + kWave * i < (PACKED ? KF : D_e))
+                            as[(PACKED ? 0 : D_t) + lane + kWave * i] = ab[e][i];
 #pragma unroll
-                    for (int i = 0; i < CT; ++i)
+                    for (int i = 0; i < (PACKED ? 0 : CT); ++i)
                         if (lane + kWave * i < D_t)
                             as[lane + kWave * i] = ab[e][CE + i];
                     if (KF + lane < KFC * 16)   // the chunks' zero padding
@@ -2640,22 +2650,22 @@ __device__ __forceinline__ void attn_agg_block(const AttnArgs &g, float *lds, in
     }
 }
 
-template <int NBM, int CE>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 && CE <= 3 ? 4 : 2))) void k_attn_agg(AttnArgs g)
+template <int NBM, bool PACKED>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 ? 4 : 2))) void k_attn_agg(AttnArgs g)
 {
     extern __shared__ float lds[];
-    attn_agg_block<NBM, CE>(g, lds, blockIdx.x);
+    attn_agg_block<NBM, PACKED>(g, lds, blockIdx.x);
 }
 
 // with the gather of the next iteration's fetch on the blocks past n_attn
 // (dispatched last: they take the CUs the attention's tail leaves free)
-template <int NBM, int CE>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 && CE <= 3 ? 4 : 2))) void k_attn_agg_gather(
+template <int NBM, bool PACKED>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NBM <= 10 ? 4 : 2))) void k_attn_agg_gather(
     AttnArgs g, int n_attn, GatherPlan gp)
 {
     extern __shared__ float lds[];
     if ((int)blockIdx.x < n_attn) {
-        attn_agg_block<NBM, CE>(g, lds, blockIdx.x);
+        attn_agg_block<NBM, PACKED>(g, lds, blockIdx.x);
         return;
     }
     gather_blocks(gp, (int)blockIdx.x - n_attn, (int)gridDim.x - n_attn, blockDim.x >> 6,
@@ -2691,11 +2701,12 @@ bool attn_lds_opt_in(int bytes, int fold_bytes, int agg_bytes)
 {
     if (agg_bytes > 0) {
         const void *fa[] = {
-            (const void *)k_attn_agg<4, 3>, (const void *)k_attn_agg<10, 3>,
-            (const void *)k_attn_agg<16, 3>, (const void *)k_attn_agg<10, 4>,
-            (const void *)k_attn_agg<16, 4>, (const void *)k_attn_agg_gather<4, 3>,
-            (const void *)k_attn_agg_gather<10, 3>, (const void *)k_attn_agg_gather<16, 3>,
-            (const void *)k_attn_agg_gather<10, 4>, (const void *)k_attn_agg_gather<16, 4>};
+            (const void *)k_attn_agg<4, false>, (const void *)k_attn_agg<10, false>,
+            (const void *)k_attn_agg<16, false>, (const void *)k_attn_agg<4, true>,
+            (const void *)k_attn_agg<10, true>, (const void *)k_attn_agg<16, true>,
+            (const void *)k_attn_agg_gather<4, false>, (const void *)k_attn_agg_gather<10, false>,
+            (const void *)k_attn_agg_gather<16, false>, (const void *)k_attn_agg_gather<4, true>,
+            (const void *)k_attn_agg_gather<10, true>, (const void *)k_attn_agg_gather<16, true>};
         for (const void *f : fa)
             if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, agg_bytes) !=
                 hipSuccess)
@@ -2803,7 +2814,7 @@ bool attn_agg_fits(const tgm_model *m)
 {
     const int KF = m->D_e + m->D_t;
     return m->nb >= 1 && m->nb <= 16 && m->M % 4 == 0 && m->M <= 112 && m->H >= 1 &&
-           m->H <= kAggMaxH && m->M % m->H == 0 && KF >= 1 && KF <= kAggMaxKF &&
+           m->H <= kAggMaxH && m->M % m->H == 0 && KF >= 1 && KF <= kAggCols * kWave &&
            m->D_t <= kAggTCols * kWave && m->KFC <= kAggUT * kMaxWaves &&
            m->VNB <= kMaxWaves && m->ONB <= kMaxWaves && m->DC <= kAggDC &&
            m->OC <= kAggMaxKC && m->KFC <= kAggMaxKC &&
@@ -3301,29 +3312,31 @@ tgm_status_t launch_attn(const tgm_model *m, const AttnArgs &a, const GatherPlan
     const dim3 block(64 * kMaxWaves);
     if (m->agg) {
         const size_t lds = attn_agg_lds(m);
-        // the registers' slot rows: up to 4, 10 or 16 slots of up to 192 edge
-        // features, or 10 or 16 of up to 256
+        // the registers' slot rows: up to 4, 10 or 16 slots, packed past 192
+        // edge features
         const bool ride = next && next->cap > 0;
         // one gather block per CU after the attention's blocks
         const dim3 grid(n_attn + (ride ? kCUs : 0));
-#define TGM_AGG(NBM, CE)                                                                       \
+#define TGM_AGG(NBM, P)                                                                        \
     do {                                                                                       \
         if (ride)                                                                              \
-            TGM_LAUNCH((k_attn_agg_gather<NBM, CE>), grid, block, lds, s, a, n_attn, *next);   \
+            TGM_LAUNCH((k_attn_agg_gather<NBM, P>), grid, block, lds, s, a, n_attn, *next);    \
         else                                                                                   \
-            TGM_LAUNCH((k_attn_agg<NBM, CE>), grid, block, lds, s, a);                         \
+            TGM_LAUNCH((k_attn_agg<NBM, P>), grid, block, lds, s, a);                          \
     } while (0)
-        const bool narrow = m->D_e <= 3 * kWave;
-        if (narrow && a.nb <= 4)
-            TGM_AGG(4, 3);
-        else if (narrow && a.nb <= 10)
-            TGM_AGG(10, 3);
-        else if (narrow)
-            TGM_AGG(16, 3);
+        const bool packed = m->D_e > (kAggCols - kAggTCols) * kWave;
+        if (a.nb <= 4 && packed)
+            TGM_AGG(4, true);
+        else if (a.nb <= 4)
+            TGM_AGG(4, false);
+        else if (a.nb <= 10 && packed)
+            TGM_AGG(10, true);
         else if (a.nb <= 10)
-            TGM_AGG(10, 4);
+            TGM_AGG(10, false);
+        else if (packed)
+            TGM_AGG(16, true);
         else
-            TGM_AGG(16, 4);
+            TGM_AGG(16, false);
 #undef TGM_AGG
         return TGM_OK;
     }
