@@ -354,13 +354,17 @@ def work_model(wl, rows, model="tgn", inplace=False):
     k["k_mit_prep"] = dict(flops=0, bytes=n_U * (4 + 8 + 8 + nb * 16 + nb * 4 + 4))
     k["k_mit_select"] = dict(flops=0, bytes=n_U * 8 * 9)
     k["k_mit_omega"] = dict(flops=0, bytes=n_U * (8 + 4 + nb * 4))
-    # the attention with the query folded into the key weights, and the one
-    # that aggregates the slot rows before projecting them, compute the same
-    # embedding: the same algorithmic work (they execute less of it)
-    k["k_attn_fold"] = dict(k["k_attn"])
-    k["k_attn_fold_gather"] = dict(k["k_attn_gather"])
-    k["k_attn_agg"] = dict(k["k_attn"])
-    k["k_attn_agg_gather"] = dict(k["k_attn_gather"])
+    # the attention with the query folded into the key weights: per root U, per
+    # slot the values and a score a head; and the one that aggregates the slot
+    # rows before projecting them: per root U, the value and the output
+    # projection, per slot and head a dot product and a weighted row.  Each is
+    # counted by its own algorithm, not by the slots' keys and values of k_attn.
+    KF, H = D_e + D_t, wl.H
+    fold = slots * (2 * KF * M + 2 * KF * H + 4 * M) + R * (2 * KF * M + 4 * M * M)
+    agg = slots * (4 * KF * H + 4 * M) + R * (4 * KF * M + 4 * M * M)
+    for name, flops in (("k_attn_fold", fold), ("k_attn_agg", agg)):
+        k[name] = dict(k["k_attn"], flops=flops)
+        k[name + "_gather"] = dict(k["k_attn_gather"], flops=flops)
     return k
 
 
@@ -440,10 +444,10 @@ def pmc_summary(fetch_csv, write_csv, copy_mib, workload, mfma_csv=None):
     what it reads for the plain copy of copy_mib MiB (a kernel that moves
     exactly that many bytes each way), so the figures are calibrated HBM
     bytes.  With a third run's SQ_INSTS_VALU_MFMA_MOPS_F32 (512 flop per
-    count) the record also holds the MFMA work each launch executes, which
-    can be less than the algorithmic work where a kernel restates the
-    contraction.  The result is keyed to a hash of the kernel sources: once
-    those change, the bench reports traffic as unmeasured again."""
+    count) the record also holds the MFMA work each launch executes, with the
+    padding of its tiles and without what the vector units do.  The result is
+    keyed to a hash of the kernel sources: once those change, the bench reports
+    traffic as unmeasured again."""
     import csv
     import re
     assert copy_mib > 0, "--copy-probe-mib must give the size of the calibration copy"
@@ -856,7 +860,8 @@ def main():
                 ex = pmc.get("mfma_flops_per_launch")
                 if mfma and ex:
                     # what the matrix cores execute per launch (counter run of
-                    # the same sources), beside the algorithmic work
+                    # the same sources), padding included, beside the algorithmic
+                    # work (of which the vector units do a part)
                     ach = ex / (dk["avg_us"] * 1e-6) / 1e12
                     executed = {"flops_per_launch": ex, "achieved": ach,
                                 "frac": ach / FP32_MFMA_PEAK_TFS}

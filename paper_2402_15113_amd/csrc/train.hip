@@ -25,9 +25,9 @@
 // batch of 4,000 (12,000 roots, 10 slots each, M = 100, 386-wide rows) 5.6
 // GFLOP instead of 46, and neither the slot rows (185 MB) nor their keys and
 // values are stored.  Two iterations of the training loop at that size took
-// 5.20 ms with products over slots and a launch (or two) per product, and
-// 1.81 ms with these, grouped eight launches to a step; one step at a batch
-// of 600: 919 and 229 us.
+// 5.35 ms with products over slots and a launch (or two) per product, and
+// 1.71 ms with these, grouped eight launches to a step; one step at a batch
+// of 600: 966 and 218 us.
 // Rows too wide for a wavefront's registers, and many heads, take the products
 // over slots (slot_form).
 #include <hip/hip_runtime.h>
