@@ -853,7 +853,9 @@ def main():
         peak = FP32_MFMA_PEAK_TFS if mfma else HBM_PEAK_GBS
         traffic = executed = None
         pmc_path = os.path.join(ROOT, "profiles", f"{dom}_{wl.name}_pmc.json")
-        if os.path.exists(pmc_path):
+        # (the counter runs are the TGN stage's: other templates and inputs of a
+        # kernel move and multiply something else)
+        if args.model == "tgn" and not (args.mitigate or args.train) and os.path.exists(pmc_path):
             pmc = json.load(open(pmc_path))
             if pmc.get("source_hash") == source_hash(*pmc.get("sources", [])):
                 traffic = pmc.get("hbm_bytes_per_launch")
